@@ -15,16 +15,15 @@
 // list back to front from the last position any pixel of the tile blended (each
 // wavefront starts at the last position its own pixels blended).  Each pixel
 // recovers its transmittance with one reciprocal per Gaussian and keeps the colour
-// accumulated behind it.  Per Gaussian, nine per-pixel values (the moments of
-// dL/d(exponent) over dx, dy, dx^2, dx dy, dy^2, then opacity and colour partials)
-// are summed across the wavefront by a reduce-scatter (CDNA4 permlane swaps across
-// halves and row pairs, then DPP exchanges within rows; the Gaussians a wavefront
-// blends are taken two at a time, sharing the last levels) and across the wavefronts
-// with LDS adds; the moments become centre and conic partials once per tile, and each
-// workgroup issues one global atomic per (tile, Gaussian, component) instead of
-// one per (pixel, Gaussian, component), consecutive lanes taking consecutive
-// components so a wavefront's atomics share cache lines.  Wavefronts in which no
-// pixel blended a Gaussian skip it.
+// accumulated behind it.  Per Gaussian, nine sums over the block's pixels (the moments
+// of dL/d(exponent) over dx, dy, dx^2, dx dy, dy^2, then opacity and colour partials)
+// are formed eight Gaussians at a time from a panel in LDS (see kPanel) and added to
+// the tile's totals there; the moments become centre and conic partials once per tile,
+// and each workgroup issues one global atomic per (tile, Gaussian, component) instead
+// of one per (pixel, Gaussian, component), consecutive lanes taking consecutive
+// components so a wavefront's atomics share cache lines.
+#include <type_traits>
+
 #include "gs_internal.h"
 
 #pragma clang fp contract(off)
@@ -36,6 +35,11 @@ namespace {
 // scalar mask instead of round-tripping it through a vector register).
 __device__ inline uint64_t wave_mask(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
+
+// Set bits of a wave-wide mask below this lane.
+__device__ inline int mask_rank(uint64_t m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
 
 // Tile of workgroup b.  Workgroups are dealt to the chip's 8 XCDs round-robin (b
 // runs on XCD b mod 8, each XCD with its own L2); XCD x takes the runs x, x + 8,
@@ -50,21 +54,31 @@ __device__ inline int xcd_raster_tile(int b) {
   return ((q / kXcdRun) * 8 + x) * kXcdRun + q % kXcdRun;
 }
 
+// View of a (wave-uniform) tile: lane v looks at view v's first tile (at most 64
+// views), so one load's latency instead of a chain of them.
 __device__ inline int view_of_tile(const ViewDev* __restrict__ views, int V, int tile) {
-  int v = 0;
-  while (v + 1 < V && tile >= views[v + 1].tile_off) ++v;
-  return v;
+  static_assert(GS_MAX_VIEWS <= 64, "one lane per view");
+  const int v = (int)__lane_id();
+  return __popcll(wave_mask(v < V && tile >= views[v < V ? v : 0].tile_off)) - 1;
 }
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
-// Base-2 exponent of the 2D Gaussian at offset (dx, dy): with A = -a/2, B = -b,
-// C = -c/2 pre-scaled by log2(e), e^power = 2^result, taken as
+// Negated base-2 exponent q of the 2D Gaussian at offset (dx, dy): with A = a/2,
+// B = b, C = c/2 pre-scaled by log2(e), e^power = 2^-q, taken as
 // dx (A dx + B dy) + C dy^2 (five operations).
-__device__ inline float gauss_power2(float A, float B, float C, float dx, float dy) {
+__device__ inline float gauss_q(float A, float B, float C, float dx, float dy) {
   return __fmaf_rn(C * dy, dy, dx * __fmaf_rn(B, dy, A * dx));
 }
+
+// The pixel test tau <= power <= 0 as one comparison: t = -tau log2(e) >= 0 and q
+// compared as unsigned integers.  A q in [0, t] orders like its bits; a negative q
+// (power > 0) has the sign bit set and a NaN lies above every number, so both fail.
+// (q is never -0: a difference of equal numbers and a sum of a -0 product with +0
+// are +0.)  One VALU comparison costs four cycles per wavefront, a multiply or an
+// add two.
+__device__ inline bool passes(float q, float t) { return __float_as_uint(q) <= __float_as_uint(t); }
 
 struct TileGeom {
   int v, tx, ty, lx, ly, px, py;
@@ -95,58 +109,66 @@ __device__ inline TileGeom tile_geom(const ViewDev* __restrict__ views, int V, i
 }
 
 // Stage record `rid` for a tile with origin (ox, oy): centre relative to the tile,
-// exponent coefficients and cutoff in base-2 units (the exponent's sign and the
-// cutoff test are unchanged by the positive factor), opacity, colour, and two
-// values for the block test below: the slope kC = -b / c of the line on which the
-// exponent peaks along vertical lines, and a cutoff tau_c = tau' (1 + 1e-5 kappa)
-// slightly below the pixel test's, kappa = (sqrt(ac) + |b|)^2 / (ac - b^2) bounding
-// (|A dx^2| + |B dx dy| + |C dy^2|) / |exponent|, so that fp32 rounding in either
-// test can never make the block test drop a Gaussian a pixel accepts.  det = ac - b^2
-// is one fused multiply-add (error below ulp(b^2), so below 2e-4 det wherever
-// kappa < 1e4, and every conic with det <= 0 yields det < ulp(b^2), kappa > 1e4);
-// kappa and kC are fp32 too (their errors only move the margin by as much of itself).
-// A conic that is not clearly positive definite (det <= 0 or kappa >= 1e4) gets
-// tau_c = -inf, so every block lists it.
-//   q0 = (u', w', A, B)   q1 = (C, tau', tau_c, kC)   q2 = (o, r, g, b)
+// coefficients of q and the cutoff t in base-2 units (the comparisons are unchanged
+// by the positive factor), opacity, colour, and two values for the block test below:
+// the slope kC = -b / c of the line on which the exponent peaks along vertical
+// lines, and a cutoff t_c = t (1 + 1e-5 kappa) slightly above the pixel test's,
+// kappa = (sqrt(ac) + |b|)^2 / (ac - b^2) bounding (|A dx^2| + |B dx dy| + |C dy^2|) /
+// |q|, so that fp32 rounding in either test can never make the block test drop a
+// Gaussian a pixel accepts.  det = ac - b^2 is one fused multiply-add (error below
+// ulp(b^2), so below 2e-4 det wherever kappa < 1e4, and every conic with det <= 0
+// yields det < ulp(b^2), kappa > 1e4); kappa and kC are fp32 too (their errors only
+// move the margin by as much of itself).  A conic that is not clearly positive
+// definite (det <= 0 or kappa >= 1e4) gets t_c = inf, so every block lists it; a
+// cutoff above 0 (opacity below 1/255) gets t_c = -1, so no block does.
+//   q0 = (u', w', A, B)   q1 = (C, t, t_c, kC)   q2 = (o, r, g, b)
 // (the per-pixel test reads q0 and q1.xy, a blend q2).
-__device__ inline void stage(const Record* __restrict__ rec, uint32_t rid, double ox, double oy, float4& q0,
-                             float4& q1, float4& q2) {
+struct RawRecord {
+  double2 uw;
+  float4 c, d;
+};
+
+__device__ inline RawRecord fetch(const Record* __restrict__ rec, uint32_t rid) {
   const Record* r = rec + rid;
-  const double2 uw = *reinterpret_cast<const double2*>(r);
-  const float4 c = reinterpret_cast<const float4*>(r)[1];
-  const float4 d = reinterpret_cast<const float4*>(r)[2];
+  return RawRecord{*reinterpret_cast<const double2*>(r), reinterpret_cast<const float4*>(r)[1],
+                   reinterpret_cast<const float4*>(r)[2]};
+}
+
+__device__ inline void stage(const RawRecord& r, double ox, double oy, float4& q0, float4& q1, float4& q2) {
+  const float4 c = r.c, d = r.d;
   const float det = __fmaf_rn(c.x, c.z, -(c.y * c.y));
-  const float tau2 = d.x * kLog2e;
-  float tc = -INFINITY, kc = 0.0f;
+  const float t = fabsf(d.x * kLog2e);
+  float tc = INFINITY, kc = 0.0f;
   if (det > 0.0f) {
     const float s = __builtin_amdgcn_sqrtf(c.x * c.z) + fabsf(c.y);
     const float kappa = (s * s) * __builtin_amdgcn_rcpf(det);
-    if (kappa < 1e4f) tc = tau2 * (1.0f + 1e-5f * kappa);
+    if (kappa < 1e4f) tc = t * (1.0f + 1e-5f * kappa);
     kc = -c.y * __builtin_amdgcn_rcpf(c.z);
   }
-  q0 = make_float4((float)(uw.x - ox), (float)(uw.y - oy), (-0.5f * c.x) * kLog2e, (-c.y) * kLog2e);
-  q1 = make_float4((-0.5f * c.z) * kLog2e, tau2, tc, kc);
+  if (!(d.x <= 0.0f)) tc = -1.0f;
+  q0 = make_float4((float)(r.uw.x - ox), (float)(r.uw.y - oy), (0.5f * c.x) * kLog2e, c.y * kLog2e);
+  q1 = make_float4((0.5f * c.z) * kLog2e, t, tc, kc);
   q2 = make_float4(c.w, d.y, d.z, d.w);
 }
 
 // Placeholder for an entry that belongs to no Gaussian (never for a consistent
-// sort): no pixel accepts it and no block lists it.
+// sort): no block lists it, and no pixel would accept it.
 __device__ inline void stage_empty(float4& q0, float4& q1, float4& q2) {
-  q0 = make_float4(0.f, 0.f, 0.f, 0.f);
-  q1 = make_float4(0.f, 1.f, INFINITY, 0.f);
+  q0 = make_float4(NAN, 0.f, 0.f, 0.f);
+  q1 = make_float4(0.f, 0.f, -1.f, 0.f);
   q2 = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
 // Ballots of the staged records [0, m) whose cutoff ellipse meets this wavefront's
 // 8x8 block of pixel centres [qx, qx + 7] x [qy, qy + 7] (tile-relative); bit b
 // of mask[k] is record 64 k + b.  The pixels' offsets u' - x, w' - y fill the box
-// [x0, x1] x [y0, y1] (same fp32 subtractions as the pixel test), and the largest
-// exponent over that box lies on the edge dx = xn (the box's nearest value to 0),
-// where it peaks at dy = kC xn, or on the edge dy = yn, peak dx = kA yn (a concave
-// quadratic's maximum over a box is at its centre, or on an edge next to the
-// nearest corner); any point of the box bounds that maximum from below, so the
-// rounding of the peak positions only costs the second-order loss already
-// covered by tau_c.
+// [x0, x1] x [y0, y1] (same fp32 subtractions as the pixel test), and the smallest
+// q over that box lies on the edge dx = xn (the box's nearest value to 0), where it
+// is least at dy = kC xn, or on the edge dy = yn, least at dx = kA yn (a convex
+// quadratic's minimum over a box is at its centre, or on an edge next to the
+// nearest corner); any point of the box bounds that minimum from above, so the
+// rounding of those positions only costs the second-order loss already covered by
+// t_c.
 template <int NM>
 __device__ inline void block_masks(const float4* s0, const float4* s1, int m, float qx, float qy,
                                       uint64_t (&mask)[NM]) {
@@ -166,9 +188,9 @@ __device__ inline void block_masks(const float4* s0, const float4* s1, int m, fl
       const float ka = (-0.5f * a0.w) * __builtin_amdgcn_rcpf(a0.z);
       const float dy1 = __builtin_amdgcn_fmed3f(xn * a1.w, y0, y1);
       const float dx2 = __builtin_amdgcn_fmed3f(yn * ka, x0, x1);
-      const float f1 = gauss_power2(a0.z, a0.w, a1.x, xn, dy1);
-      const float f2 = gauss_power2(a0.z, a0.w, a1.x, dx2, yn);
-      hit = fmaxf(f1, f2) >= a1.z;
+      const float f1 = gauss_q(a0.z, a0.w, a1.x, xn, dy1);
+      const float f2 = gauss_q(a0.z, a0.w, a1.x, dx2, yn);
+      hit = fminf(f1, f2) <= a1.z;
     }
     mask[k] = wave_mask(hit);
   }
@@ -212,7 +234,7 @@ __global__ __launch_bounds__(T * T) void k_render_fwd(const ViewDev* __restrict_
     if (threadIdx.x < m) {
       const uint32_t rid = pair_rec[base + threadIdx.x];
       if (rid < n_rec) {
-        stage(rec, rid, tg.ox, tg.oy, s0[threadIdx.x], s1[threadIdx.x], s2[threadIdx.x]);
+        stage(fetch(rec, rid), tg.ox, tg.oy, s0[threadIdx.x], s1[threadIdx.x], s2[threadIdx.x]);
       } else {
         stage_empty(s0[threadIdx.x], s1[threadIdx.x], s2[threadIdx.x]);
       }
@@ -232,11 +254,11 @@ __global__ __launch_bounds__(T * T) void k_render_fwd(const ViewDev* __restrict_
           const float4 a0 = s0[j];
           const float4 a1 = s1[j];
           const float dx = a0.x - fx, dy = a0.y - fy;
-          const float p2 = gauss_power2(a0.z, a0.w, a1.x, dx, dy);
-          const bool pass = p2 <= pmax && p2 >= a1.y;
+          const float q = gauss_q(a0.z, a0.w, a1.x, dx, dy);
+          const bool pass = pmax == 0.0f && passes(q, a1.y);
           if (wave_mask(pass) != 0ull) {
             const float4 a2 = s2[j];
-            const float alpha = fminf(kAlphaMax, a2.x * __builtin_amdgcn_exp2f(p2));
+            const float alpha = fminf(kAlphaMax, a2.x * __builtin_amdgcn_exp2f(-q));
             const float Tn = Tr * (1.0f - alpha);
             const bool stop = pass && Tn < kTMin;
             const bool blend = pass && !stop;
@@ -289,31 +311,9 @@ __global__ __launch_bounds__(T * T) void k_render_fwd(const ViewDev* __restrict_
   }
 }
 
-// a + b across the two halves of the wave: lanes 0-31 receive the sum of a over
-// lanes l and l + 32, lanes 32-63 the sum of b (v_permlane32_swap, CDNA4).
-__device__ inline float fold32(float a, float b) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// The same across row pairs: rows (0, 1) and (2, 3) of 16 lanes; row 0 and row 2
-// keep a, rows 1 and 3 keep b (v_permlane16_swap, CDNA4).
-__device__ inline float fold16(float a, float b) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// x plus lane l ^ 16's x (the partner row within each half of the wave), through the
-// LDS crossbar (ds_swizzle, no memory access) rather than a VALU swap: the ninth
-// values need only the rows that the even rows end up with.
-__device__ inline float add_row_pair(float x) {
-  // bit mode: and_mask 0x1f, or_mask 0, xor_mask 0x10
-  return x + __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(x), 0x401F));
-}
-
-// Lane l receives v from the lane the DPP control names (row_ror:8 = 0x128: lane
-// l ^ 8 of its row; row_half_mirror = 0x141: lane 7 - l of its half-row;
-// quad_perm [2,3,0,1] = 0x4E and [1,0,3,2] = 0xB1: lanes l ^ 2 and l ^ 1).
+// Lane l receives v from the lane the DPP control names (row_half_mirror = 0x141:
+// lane 7 - l of its half-row; quad_perm [2,3,0,1] = 0x4E and [1,0,3,2] = 0xB1: lanes
+// l ^ 2 and l ^ 1).
 template <int CTRL>
 __device__ inline float dpp(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
@@ -328,113 +328,52 @@ __device__ inline float fold_dpp(float a, float b, bool hi) {
   return own + dpp<CTRL>(give);
 }
 
-// fold_dpp for a selector that is a DPP bank bit (bit 3: banks 2 and 3 of each row;
-// bit 2: banks 1 and 3), without the two selects: every lane forms a plus its
-// partner's a, then the lanes of the selected banks overwrite that with b plus the
-// partner's b (a DPP add that writes those banks only).  A DPP read of a VGPR that
-// the VALU wrote in the last two cycles needs two wait states, and the compiler
-// does not see inside the asm: the nops before and after cover the asm's own read
-// and any DPP read of its result.  The same sums in the same order as fold_dpp.
-__device__ inline float fold_ror8_bit3(float a, float b) {
-  float t = a + dpp<0x128>(a);
-  asm("s_nop 1\n\tv_add_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xc bound_ctrl:1\n\ts_nop 1" : "+v"(t) : "v"(b));
-  return t;
-}
+// The same across half-row mirrors, selected by lane bit 2 (DPP banks 1 and 3),
+// without the two selects: every lane forms a plus its partner's a, then the lanes
+// of the selected banks overwrite that with b plus the partner's b (a DPP add that
+// writes those banks only).  A DPP read of a VGPR that the VALU wrote in the last two
+// cycles needs two wait states, and the compiler does not see inside the asm: the
+// nops before and after cover the asm's own read and any DPP read of its result.
 __device__ inline float fold_mirror_bit2(float a, float b) {
   float t = a + dpp<0x141>(a);
   asm("s_nop 1\n\tv_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa bound_ctrl:1\n\ts_nop 1" : "+v"(t) : "v"(b));
   return t;
 }
 
-// Reduce-scatter of nine per-lane values over the wave, added into an LDS row.
-// Each level halves the registers by pairing lanes whose selector bit differs
-// (across wave halves, across row pairs, across half-rows, across the halves of
-// each half-row by mirroring), then quad permutations finish the sums.  The first
-// eight values go through the first three levels on their own (reduce8_part);
-// the ninth joins there.  A record alone (reduce9_tail) ends with every group of
-// four lanes holding one total, and the lane of each group with slot >= 0 adds it
-// into LDS (nine lanes, one instruction): with r = row, h = lane bit 3, q = lane
-// bit 2, value {0, 2, 1, 3}[r] + 4h sits where q = 0 and value 8 where r = h = 0,
-// q = 1.  Two records (reduce18_tail) share the last three levels: every pair of
-// lanes then holds one of the 18 totals (the second record's at lane bit 2 set,
-// both ninth values at lane bit 1 set), which costs 45 instructions instead of 56.
-typedef __attribute__((address_space(3))) float LdsFloat;
+// The backward's sums over pixels.  Each wavefront walks its candidates pixel by
+// lane and writes, per (candidate, pixel), the two numbers every partial is made of,
+// dL/d(exponent) and the blend weight, into its own LDS panel of kPanel candidates x
+// 64 pixels.  When the panel is full the wavefront turns round: lane l takes
+// candidate l / 8 and row l mod 8 of the 8x8 block, and forms the row's nine sums from
+// eight pixels read back with four 16-byte loads, with no cross-lane step; three DPP
+// levels over the candidate's eight lanes finish them, each lane ending with one of
+// the eight first totals.  Per candidate this is about 27 VALU cycles, against
+// about 118 for summing every candidate's nine values across 64 lanes (permlane
+// swaps take 8 cycles, DPP and selects 4, a multiply or an add 2).
+// LDS float adds cost three cycles a lane on this chip (193 for a full wavefront);
+// double adds cost 8 for the wavefront, so the tile's totals are doubles.
+constexpr int kPanel = 8;
+// Candidates whose tests and alphas a wavefront takes together (each wavefront's
+// chain per candidate is long, and four wavefronts per SIMD hide it only in part):
+// 1, 2 or 4 at a time took 1.48, 1.33 and 1.26 ms at 1M Gaussians and 10 Mpix, and
+// 117, 86 and 76 us at 10k Gaussians and 128x128 pixels.
+constexpr int kGroup = 4;
+typedef __attribute__((address_space(3))) double LdsDouble;
 
-__device__ inline float reduce8_part(const float (&v)[kGrad2D]) {
-  const float b0 = fold32(v[0], v[1]);
-  const float b1 = fold32(v[2], v[3]);
-  const float b2 = fold32(v[4], v[5]);
-  const float b3 = fold32(v[6], v[7]);
-  const float c0 = fold16(b0, b1);
-  const float c1 = fold16(b2, b3);
-  return fold_ror8_bit3(c0, c1);
-}
-
-__device__ inline void lds_add(uint32_t addr, float x) {
-  __hip_atomic_fetch_add((LdsFloat*)(uintptr_t)addr, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-// d = reduce8_part of the record's first eight values, v8 its ninth; lanes with
-// `add` add their total at addr (row and column included).
-__device__ inline void reduce9_tail(float d, float v8, uint32_t addr, bool add) {
-  const float c2 = add_row_pair(fold32(v8, 0.0f));
-  const float d1 = c2 + dpp<0x128>(c2);
-  float e = fold_mirror_bit2(d, d1);
-  e += dpp<0x4E>(e);
-  e += dpp<0xB1>(e);
-  if (add) lds_add(addr, e);
-}
-
-// Records a and b (parts da, db, ninth values a8, b8) reduced together; lanes that
-// hold a total of a add it at addr_a, those holding one of b at addr_b.
-__device__ inline void reduce18_tail(float da, float a8, float db, float b8, uint32_t addr_a, uint32_t addr_b,
-                                     bool add_a, bool add_b, bool bit1) {
-  const float m2 = add_row_pair(fold32(a8, b8));
-  const float m3 = m2 + dpp<0x128>(m2);
-  const float e0 = fold_mirror_bit2(da, db);
-  const float e1 = m3 + dpp<0x141>(m3);
-  float f = fold_dpp<0x4E>(e0, e1, bit1);
-  f += dpp<0xB1>(f);
-  if (add_a) lds_add(addr_a, f);
-  if (add_b) lds_add(addr_b, f);
-}
-
-// Byte offset of row j of the [NT][kGrad2D] float accumulator, formed on the scalar
-// unit (j is uniform); left to itself the compiler folds it into a 64-bit vector
-// multiply-add of the lane's address.
-__device__ inline uint32_t acc_row_offset(int j) {
-  static_assert(kGrad2D * sizeof(float) == 36, "accumulator row size");
-  uint32_t off;
-  asm("s_mul_i32 %0, %1, 36" : "=s"(off) : "s"(__builtin_amdgcn_readfirstlane(j)));
-  return off;
-}
-
-// The accumulator column reduce9_tail adds from this lane (-1: none).
-__device__ inline int reduce9_slot(unsigned lane) {
-  if (lane & 3u) return -1;
-  const unsigned r = lane >> 4, h = (lane >> 3) & 1u, q = (lane >> 2) & 1u;
-  if (q == 0u) return (int)((((r & 1u) << 1) | (r >> 1)) + 4u * h);
-  return (r == 0u && h == 0u) ? 8 : -1;
-}
-
-// The total reduce18_tail leaves in this lane for it to add: 0-8 for the first
-// record's columns, 9-17 for the second's (-1: none).
-__device__ inline int reduce18_slot(unsigned lane) {
-  if (lane & 1u) return -1;
-  const unsigned r = lane >> 4, h = (lane >> 3) & 1u, q = (lane >> 2) & 1u;
-  if ((lane & 2u) == 0u) return (int)((((r & 1u) << 1) | (r >> 1)) + 4u * h + 9u * q);
-  if (h == 0u && q == 0u && (r & 1u) == 0u) return r == 0u ? 8 : 17;
-  return -1;
-}
+// Panel position of pixel pair (row, u): pixels 2 u and 2 u + 1 of a row form a
+// 16-byte unit, and the units of a row are permuted by xor with unit_turn.  The 16
+// lanes (two slots, eight rows) that one LDS cycle serves then read 16 different
+// units of the 256-byte bank row, unit u of every row in the same load.
+__device__ inline int unit_turn(int slot, int row) { return (row >> 2) + 2 * (slot & 1); }
 
 // ORDERED: instead of adding each (tile, Gaussian) partial sum into grad2d with a
 // global atomic, write it to out[pair position * kGrad2D + component] (every
-// position of the tile's list, zeros included), each wave reducing into its own
-// LDS rows and the waves' rows summed in wave order, so that every partial is the
+// position of the tile's list, zeros included), each wave keeping its totals in its
+// own LDS rows and the waves' rows summed in wave order, so that every partial is the
 // same bits on every run; the per-Gaussian sums are then taken in tile order by
 // launch_ordered_sum.
 template <int T, bool ORDERED = false>
-__global__ __launch_bounds__(T * T) void k_render_bwd(const ViewDev* __restrict__ views, int V, int n_tiles_total,
+__global__ __launch_bounds__(T * T) __attribute__((amdgpu_waves_per_eu(4))) void k_render_bwd(const ViewDev* __restrict__ views, int V, int n_tiles_total,
                                                     const uint2* __restrict__ ranges,
                                                     const uint32_t* __restrict__ pair_rec,
                                                     const Record* __restrict__ rec, uint32_t n_rec,
@@ -442,14 +381,17 @@ __global__ __launch_bounds__(T * T) void k_render_bwd(const ViewDev* __restrict_
                                                     const uint32_t* __restrict__ last,
                                                     const float* __restrict__ dL_dcolor,
                                                     const float* __restrict__ dL_dG, float* __restrict__ grad2d) {
-  // records are staged NB at a time, half the tile's threads (at least 64): 11 KB of
-  // LDS at T = 16, so registers rather than LDS set the occupancy (8 waves per SIMD)
-  // (the ordered mode keeps one accumulator per wave: 64 records per batch)
-  constexpr int NT = T * T, NB = ORDERED ? 64 : (NT >= 128 ? NT / 2 : NT), NM = NB / 64, NW = NT / 64;
-  __shared__ float4 s0[NB], s1[NB], s2[NB];
-  __shared__ uint32_t srid[NB];
+  // records are staged NB at a time; row NB is a record no pixel accepts, which fills
+  // up a wavefront's last group
+  constexpr int NT = T * T, NB = ORDERED || NT < 128 ? 64 : 128, NM = (NB + 63) / 64, NW = NT / 64;
   constexpr int NACC = ORDERED ? NW : 1;
-  __shared__ float acc[NACC][NB][kGrad2D];
+  constexpr int G = kGroup;
+  using Acc = typename std::conditional<ORDERED, float, double>::type;
+  __shared__ float4 s0[NB + 1], s1[NB + 1], s2[NB + 1];
+  __shared__ uint32_t srid[NB];
+  __shared__ Acc acc[NACC][NB][kGrad2D];
+  __shared__ __align__(16) float2 panel[NW][kPanel][64];
+  __shared__ __align__(16) uint32_t list[NW][NB + kPanel];   // byte offsets of the wave's candidates in s0
   __shared__ uint32_t smax[NW];
   const int tile = xcd_raster_tile((int)blockIdx.x);
   if (tile >= n_tiles_total) return;
@@ -458,6 +400,7 @@ __global__ __launch_bounds__(T * T) void k_render_bwd(const ViewDev* __restrict_
   const uint2 rg = ranges[tile];
   const float fx = (float)tg.lx, fy = (float)tg.ly;
   const float qx = (float)(tg.lx & ~7), qy = (float)(tg.ly & ~7);
+  const int wave = threadIdx.x >> 6, lane = (int)__lane_id();
 
   // Sg = sum over channels of dL/dcolour times the colour accumulated behind the
   // current Gaussian (background included): the only form in which that colour
@@ -480,146 +423,224 @@ __global__ __launch_bounds__(T * T) void k_render_bwd(const ViewDev* __restrict_
   uint32_t mx = lp;
   for (int off = 32; off > 0; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off));
   const int wave_last = (int)mx;           // this wave never needs list positions >= wave_last
-  const unsigned lane = __lane_id();
-  const int slot = reduce9_slot(lane), slot18 = reduce18_slot(lane);
-  const bool bit1 = (lane & 2u) != 0u;
-  const bool add9 = slot >= 0, add_a = slot18 >= 0 && slot18 < kGrad2D, add_b = slot18 >= kGrad2D;
-  // 32-bit LDS byte addresses of this lane's columns in acc[0] for the two
-  // reductions (plain integer arithmetic in the loop: the compiler would otherwise
-  // form the address in 64 bits)
-  const uint32_t acc0 = (uint32_t)(uintptr_t)(LdsFloat*)&acc[ORDERED ? threadIdx.x / 64 : 0][0][0];
-  const uint32_t col9 = acc0 + 4u * (uint32_t)(slot < 0 ? 0 : slot);
-  const uint32_t col18 = acc0 + 4u * (uint32_t)(slot18 < 0 ? 0 : slot18 % kGrad2D);
-  if (__lane_id() == 0) smax[threadIdx.x / 64] = mx;
-  for (int i = threadIdx.x; i < NACC * NB * kGrad2D; i += NT) (&acc[0][0][0])[i] = 0.0f;
+  if (lane == 0) smax[wave] = mx;
+  for (int i = threadIdx.x; i < NACC * NB * kGrad2D; i += NT) (&acc[0][0][0])[i] = (Acc)0;
+  if (threadIdx.x == 0) stage_empty(s0[NB], s1[NB], s2[NB]);
+
+  // this lane's part in the panel's sums: slot ps, row pr, the row's upstream
+  // gradients (through the panel's own memory), the total it ends with (pc), and the
+  // selectors of the last two levels; pan[s & 1] + 64 s is where it writes as a pixel
+  const int ps = lane >> 3, pr = lane & 7;
+  const int pc = ((lane & 1) << 2) | (lane & 2) | ((lane >> 2) & 1);
+  const bool bit1 = (lane & 2) != 0, bit0 = (lane & 1) != 0;
+  float2* const pan[2] = {&panel[wave][0][lane ^ (2 * unit_turn(0, lane >> 3))],
+                          &panel[wave][0][lane ^ (2 * unit_turn(1, lane >> 3))]};
+  const float4* const prow = reinterpret_cast<const float4*>(&panel[wave][ps][8 * pr]);
+  const int turn = unit_turn(ps, pr);
+  float pg[3][8];
+  {
+    float* pf = reinterpret_cast<float*>(&panel[wave][0][0]);
+    pf[lane] = g0;
+    pf[64 + lane] = g1;
+    pf[128 + lane] = g2;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch)
+#pragma unroll
+      for (int x = 0; x < 8; ++x) pg[ch][x] = pf[64 * ch + 8 * pr + x];
+    __builtin_amdgcn_wave_barrier();
+  }
+  const float pgy = qy + (float)pr;
   __syncthreads();
   int jmax = 0;
   for (int w = 0; w < NW; ++w) jmax = max(jmax, (int)smax[w]);
 
+  // the records of a batch are fetched while the one before it is walked (at four
+  // waves per SIMD nothing else covers two dependent loads per batch)
+  uint32_t rid = ~0u;
+  RawRecord raw{};
+  const auto fetch_batch = [&](int end) {
+    const int beg = end > NB ? end - NB : 0;
+    rid = (int)threadIdx.x < end - beg ? pair_rec[rg.x + beg + threadIdx.x] : ~0u;
+    if (rid < n_rec) raw = fetch(rec, rid);
+  };
+  fetch_batch(jmax);
   for (int end = jmax; end > 0; end -= NB) {
     const int beg = end > NB ? end - NB : 0;
     const int m = end - beg;
     __syncthreads();
     if ((int)threadIdx.x < m) {
-      const uint32_t rid = pair_rec[rg.x + beg + threadIdx.x];
       srid[threadIdx.x] = rid;
       if (rid < n_rec) {
-        stage(rec, rid, tg.ox, tg.oy, s0[threadIdx.x], s1[threadIdx.x], s2[threadIdx.x]);
+        stage(raw, tg.ox, tg.oy, s0[threadIdx.x], s1[threadIdx.x], s2[threadIdx.x]);
       } else {
         stage_empty(s0[threadIdx.x], s1[threadIdx.x], s2[threadIdx.x]);
       }
     }
     __syncthreads();
+    if (beg > 0) fetch_batch(beg);
     // records this wavefront may need: positions below its own last blended one
     // whose cutoff ellipse meets its block, walked back to front
     uint64_t mask[NM];
     block_masks<NM>(s0, s1, min(m, wave_last - beg), qx, qy, mask);
     const uint32_t lrel = lp > (uint32_t)beg ? lp - (uint32_t)beg : 0u;   // batch positions this pixel blended
+    int cnt = 0;
+    bool opaque = false;
+#pragma unroll
     for (int k = NM - 1; k >= 0; --k) {
-      uint64_t mk = mask[k];
-      // blended records are reduced two at a time: the first waits (as the first
-      // three levels of its reduction and its ninth value) for the next
-      float da = 0.0f, a8 = 0.0f;
-      int ja = -1;
-      while (mk) {
-        const int b = 63 - __builtin_clzll(mk);
-        mk &= ~(1ull << b);
-        const int j = 64 * k + b;
-        const float4 a0 = s0[j];
-        const float4 a1 = s1[j];
-        const float4 a2 = s2[j];
-        const float dx = a0.x - fx, dy = a0.y - fy;
-        const float p2 = gauss_power2(a0.z, a0.w, a1.x, dx, dy);
-        const bool on = (uint32_t)j < lrel && p2 <= 0.0f && p2 >= a1.y;
-        // (a2 is fetched with a0 and a1, before the branch: one address, and the blend
-        // below waits for nothing more)
-        asm volatile("" ::"v"(a2.x), "v"(a2.y), "v"(a2.z), "v"(a2.w));
-        if (wave_mask(on) == 0ull) continue;    // no pixel of this wave blended it
-        // straight-line update; lanes that did not blend this Gaussian keep their state
-        // and contribute zeros
-        const float G = __builtin_amdgcn_exp2f(p2);
-        const float og = a2.x * G;
-        const bool capped = og > kAlphaMax;
-        // alpha of this pixel, 0 where it did not blend: then 1 / (1 - alpha) = 1
-        // exactly and transmittance and weight need no select
-        const float alpha = on ? fminf(og, kAlphaMax) : 0.0f;
-        const float ri = __builtin_amdgcn_rcpf(1.0f - alpha);
-        Tr = Tr * ri;                          // transmittance in front of this Gaussian
-        const float wgt = alpha * Tr;
-        // Per pixel: colour partials, opacity partial and the moments of the exponent's
-        // derivative dpow over (dx, dy, dx^2, dx dy, dy^2); the centre and conic
-        // partials are fixed linear maps of these moments (applied once per tile).
-        // dL/dalpha = T (g . colour) - Sg / (1 - alpha) + gG, gG being the
-        // load-balancing gradient of the pixel's soft count (each blended alpha enters
-        // it with weight 1).
-        const float cg = __fmaf_rn(g2, a2.w, __fmaf_rn(g1, a2.z, g0 * a2.y));
-        float dLda = __fmaf_rn(Tr, cg, __fmaf_rn(-Sg, ri, gG));
-        dLda = (on && !capped) ? dLda : 0.0f;  // a capped alpha has zero derivative
-        Sg = __fmaf_rn(cg, wgt, Sg);
-        const float dpow = dLda * og;           // dL/d(exponent)
-        float p[kGrad2D];
-        p[0] = dpow * dx;
-        p[1] = dpow * dy;
-        p[2] = p[0] * dx;
-        p[3] = p[0] * dy;
-        p[4] = p[1] * dy;
-        p[5] = dpow;                            // dL/dopacity = (sum of dpow) / o, formed per tile
-        p[6] = g0 * wgt;
-        p[7] = g1 * wgt;
-        p[8] = g2 * wgt;
-        const float d = reduce8_part(p);
-        if (ja < 0) {
-          da = d;
-          a8 = p[8];
-          ja = j;
+      const uint64_t mk = mask[k];
+      const int hits = __popcll(mk);
+      if ((mk >> lane) & 1ull) {
+        // its rank from the back
+        list[wave][cnt + hits - 1 - mask_rank(mk)] = 16u * (uint32_t)(64 * k + lane);
+        opaque |= s2[64 * k + lane].x > kAlphaMax;
+      }
+      cnt += hits;
+    }
+    const bool caps = wave_mask(opaque) != 0ull;   // some candidate's alpha may reach the cap
+    if (lane < kPanel) list[wave][cnt + lane] = 16u * NB;
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t lrel16 = 16u * lrel;
+    // candidates base + h .. base + h + G - 1: their tests and alphas do not depend on
+    // each other, so G of them hide each other's latency where few waves are resident
+    const auto group = [&](auto cap, int first, int h) {
+      constexpr bool CAP = decltype(cap)::value;
+        float alpha[G], ri[G], cg[G];
+        bool capped[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const uint32_t off = list[wave][first + g];
+          const float4 a0 = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(s0) + off);
+          const float2 a1 = *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(s1) + off);
+          const float4 a2 = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(s2) + off);
+          const float q = gauss_q(a0.z, a0.w, a1.x, a0.x - fx, a0.y - fy);
+          const bool on = (off < lrel16) & passes(q, a1.y);
+          const float og = a2.x * __builtin_amdgcn_exp2f(-q);
+          // alpha of this pixel, 0 where it did not blend: then 1 / (1 - alpha) = 1
+          // exactly, transmittance and weight need no select and every sum gets zeros
+          alpha[g] = on ? og : 0.0f;
+          if (CAP) {
+            capped[g] = alpha[g] > kAlphaMax;
+            alpha[g] = capped[g] ? kAlphaMax : alpha[g];
+          }
+          ri[g] = __builtin_amdgcn_rcpf(1.0f - alpha[g]);
+          cg[g] = __fmaf_rn(g2, a2.w, __fmaf_rn(g1, a2.z, g0 * a2.y));
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          Tr = Tr * ri[g];                       // transmittance in front of this Gaussian
+          const float wgt = alpha[g] * Tr;
+          // dL/dalpha = T (g . colour) - Sg / (1 - alpha) + gG, gG being the
+          // load-balancing gradient of the pixel's soft count (each blended alpha enters
+          // it with weight 1); dL/d(exponent) = alpha dL/dalpha, zero for a capped alpha
+          const float dLda = __fmaf_rn(Tr, cg[g], __fmaf_rn(-Sg, ri[g], gG));
+          Sg = __fmaf_rn(cg[g], wgt, Sg);
+          float dpow = dLda * alpha[g];
+          if (CAP) dpow = capped[g] ? 0.0f : dpow;
+          pan[(h + g) & 1][64 * (h + g)] = make_float2(dpow, wgt);
+        }
+    };
+    for (int base = 0; base < cnt; base += kPanel) {
+      // fill the panel, G candidates at a time
+#pragma unroll
+      for (int h = 0; h < kPanel; h += G) {
+        if (base + h >= cnt) break;
+        if (caps) group(std::true_type{}, base + h, h);
+        else group(std::false_type{}, base + h, h);
+      }
+      __builtin_amdgcn_wave_barrier();
+      // nine sums of this lane's row: the moments of dL/d(exponent) over (dx, dy,
+      // dx^2, dx dy, dy^2) and itself, and the colour partials
+      const uint32_t off = list[wave][base + ps];
+      const float2 uw = *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(s0) + off);
+      const float ux = uw.x - qx;
+      float m0 = 0.0f, m1 = 0.0f, m2 = 0.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float4 v = prow[i ^ turn];
+        const float dxa = ux - (float)(2 * i), dxb = ux - (float)(2 * i + 1);
+        const float ta = v.x * dxa, tb = v.z * dxb;
+        m0 += v.x;
+        m1 += ta;
+        m2 = __fmaf_rn(ta, dxa, m2);
+        c0 = __fmaf_rn(pg[0][2 * i], v.y, c0);
+        c1 = __fmaf_rn(pg[1][2 * i], v.y, c1);
+        c2 = __fmaf_rn(pg[2][2 * i], v.y, c2);
+        m0 += v.z;
+        m1 += tb;
+        m2 = __fmaf_rn(tb, dxb, m2);
+        c0 = __fmaf_rn(pg[0][2 * i + 1], v.w, c0);
+        c1 = __fmaf_rn(pg[1][2 * i + 1], v.w, c1);
+        c2 = __fmaf_rn(pg[2][2 * i + 1], v.w, c2);
+      }
+      __builtin_amdgcn_wave_barrier();   // the panel may be written again
+      const float dy = uw.y - pgy;
+      const float n0 = dy * m0, n1 = dy * m1, n2 = dy * n0;
+      // over the candidate's eight lanes: lane bits 2, 1, 0 select among the first
+      // eight values; the ninth is summed in every lane
+      const float e0 = fold_mirror_bit2(m1, n0), e1 = fold_mirror_bit2(m2, n1);
+      const float e2 = fold_mirror_bit2(n2, m0), e3 = fold_mirror_bit2(c0, c1);
+      const float f0 = fold_dpp<0x4E>(e0, e1, bit1), f1 = fold_dpp<0x4E>(e2, e3, bit1);
+      const float tot = fold_dpp<0xB1>(f0, f1, bit0);
+      c2 += dpp<0x141>(c2);
+      c2 += dpp<0x4E>(c2);
+      c2 += dpp<0xB1>(c2);
+      if (base + ps < cnt) {
+        const uint32_t j = off >> 4;
+        if (ORDERED) {
+          acc[wave][j][pc] = (Acc)tot;
+          if (pr == 0) acc[wave][j][8] = (Acc)c2;
         } else {
-          reduce18_tail(da, a8, d, p[8], col18 + acc_row_offset(ja), col18 + acc_row_offset(j), add_a, add_b, bit1);
-          ja = -1;
+          __hip_atomic_fetch_add((LdsDouble*)&acc[0][j][pc], (double)tot, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+          if (pr == 0)
+            __hip_atomic_fetch_add((LdsDouble*)&acc[0][j][8], (double)c2, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
         }
       }
-      if (ja >= 0) reduce9_tail(da, a8, col9 + acc_row_offset(ja), add9);
     }
     __syncthreads();
     if ((int)threadIdx.x < m) {
-      float* a = acc[0][threadIdx.x];
-      if (ORDERED) {
-        for (int w = 1; w < NACC; ++w)
-          for (int k = 0; k < kGrad2D; ++k) a[k] += acc[w][threadIdx.x][k];
+      Acc* ar = acc[0][threadIdx.x];
+      float a[kGrad2D];
+      for (int c = 0; c < kGrad2D; ++c) {
+        a[c] = (float)ar[c];
+        for (int w = 1; w < NACC; ++w) a[c] += (float)acc[w][threadIdx.x][c];
       }
       // moments -> partials: with exponent p = -(a dx^2 + 2 b dx dy + c dy^2)/2 and the
-      // staged coefficients A, B, C = (-a/2, -b, -c/2) log2(e):
-      // dp/du = ln2 (2A dx + B dy), dp/dw = ln2 (B dx + 2C dy),
+      // staged coefficients A, B, C = (a/2, b, c/2) log2(e):
+      // dp/du = -ln2 (2A dx + B dy), dp/dw = -ln2 (B dx + 2C dy),
       // dp/da = -dx^2/2, dp/db = -dx dy, dp/dc = -dy^2/2
       const float A = s0[threadIdx.x].z, B = s0[threadIdx.x].w, C = s1[threadIdx.x].x;
-      const float m1 = a[0], m2 = a[1], m3 = a[2], m4 = a[3], m5 = a[4];
-      a[0] = kLn2 * (2.0f * A * m1 + B * m2);
-      a[1] = kLn2 * (B * m1 + 2.0f * C * m2);
-      a[2] = -0.5f * m3;
-      a[3] = -m4;
-      a[4] = -0.5f * m5;
+      ar[0] = (Acc)(-kLn2 * (2.0f * A * a[0] + B * a[1]));
+      ar[1] = (Acc)(-kLn2 * (B * a[0] + 2.0f * C * a[1]));
+      ar[2] = (Acc)(-0.5f * a[2]);
+      ar[3] = (Acc)(-a[3]);
+      ar[4] = (Acc)(-0.5f * a[4]);
       // dL/dopacity: the exponent derivative summed over the tile's pixels is
       // sum dL/dalpha o G, so dividing by o gives sum dL/dalpha G
       const float o = s2[threadIdx.x].x;
-      a[5] = o > 0.0f ? a[5] / o : 0.0f;
+      ar[5] = (Acc)(o > 0.0f ? a[5] / o : 0.0f);
+      for (int c = 6; c < kGrad2D; ++c) ar[c] = (Acc)a[c];
     }
     __syncthreads();
     // one global atomic per (tile, Gaussian, component); consecutive lanes take
     // consecutive components, so a wavefront's atomics fall on a few cache lines
     // (element offsets in 64 bits: n_rec * 9 may pass 2^32 bytes)
-    float* af = &acc[0][0][0];
+    Acc* af = &acc[0][0][0];
     if (ORDERED) {
       float* po = grad2d + ((size_t)rg.x + (size_t)beg) * kGrad2D;
-      for (int i = threadIdx.x; i < m * kGrad2D; i += NT) po[i] = srid[i / kGrad2D] < n_rec ? af[i] : 0.0f;
+      for (int i = threadIdx.x; i < m * kGrad2D; i += NT) po[i] = srid[i / kGrad2D] < n_rec ? (float)af[i] : 0.0f;
       __syncthreads();
-      for (int i = threadIdx.x; i < NACC * NB * kGrad2D; i += NT) af[i] = 0.0f;
+      for (int i = threadIdx.x; i < NACC * NB * kGrad2D; i += NT) af[i] = (Acc)0;
     } else {
       for (int i = threadIdx.x; i < m * kGrad2D; i += NT) {
         const int j = i / kGrad2D;
-        const uint32_t rid = srid[j];
-        const float x = af[i];
-        if (x != 0.0f && rid < n_rec)
-          unsafeAtomicAdd(grad2d + ((size_t)rid * kGrad2D + (size_t)(i - kGrad2D * j)), x);
-        af[i] = 0.0f;
+        const uint32_t r = srid[j];
+        const float x = (float)af[i];
+        if (x != 0.0f && r < n_rec)
+          unsafeAtomicAdd(grad2d + ((size_t)r * kGrad2D + (size_t)(i - kGrad2D * j)), x);
+        af[i] = (Acc)0;
       }
     }
   }
