@@ -1,15 +1,12 @@
 // Tile rasterizer forward and backward for gfx950.
 //
-// Forward (Sec. III Eq. 2): one workgroup of T x T threads per T x T tile
-// (T = 8, 16 or 32), one thread per pixel, each wavefront owning an 8x8 block.
-// The tile's depth-ordered list is walked in batches of T^2 records staged in LDS;
-// every pixel reads each staged record by LDS broadcast, so a record fetched from
-// HBM once serves the whole tile.  Each wavefront tests the staged batch against
-// its block (one record per lane, one ballot per 64 records: does the cutoff
-// ellipse meet the block's pixel centres) and walks only the records that do.  A wavefront stops when all its pixels have stopped
-// blending, the workgroup when all have.  Screen centres arrive in FP64 and are
-// made relative to the tile origin while staging, so per-pixel offsets are
-// accurate fp32 numbers at any image size.
+// Forward (Sec. III Eq. 2): one thread per pixel, each wavefront owning an 8x8 block
+// of a T x T tile (T = 8, 16 or 32).  It walks the tile's depth-ordered list, one
+// record per lane, keeps the records whose cutoff ellipse meets the block's pixel
+// centres in its own LDS rows, and every pixel reads these by LDS broadcast.  A
+// wavefront stops when all its pixels have stopped blending.  Screen centres arrive
+// in FP64 and are made relative to the tile origin while staging, so per-pixel
+// offsets are accurate fp32 numbers at any image size.
 //
 // Backward (Sec. IV-E): the same tiling and per-block candidate sets, walking each
 // list back to front from the last position any pixel of the tile blended (each
@@ -159,16 +156,31 @@ __device__ inline void stage_empty(float4& q0, float4& q1, float4& q2) {
   q2 = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
-// Ballots of the staged records [0, m) whose cutoff ellipse meets this wavefront's
-// 8x8 block of pixel centres [qx, qx + 7] x [qy, qy + 7] (tile-relative); bit b
-// of mask[k] is record 64 k + b.  The pixels' offsets u' - x, w' - y fill the box
-// [x0, x1] x [y0, y1] (same fp32 subtractions as the pixel test), and the smallest
-// q over that box lies on the edge dx = xn (the box's nearest value to 0), where it
-// is least at dy = kC xn, or on the edge dy = yn, least at dx = kA yn (a convex
-// quadratic's minimum over a box is at its centre, or on an edge next to the
-// nearest corner); any point of the box bounds that minimum from above, so the
+// Does a staged record's cutoff ellipse meet this wavefront's 8x8 block of pixel
+// centres [qx, qx + 7] x [qy, qy + 7] (tile-relative)?  The pixels' offsets u' - x,
+// w' - y fill the box [x0, x1] x [y0, y1] (same fp32 subtractions as the pixel test),
+// and the smallest q over that box lies on the edge dx = xn (the box's nearest value
+// to 0), where it is least at dy = kC xn, or on the edge dy = yn, least at dx = kA yn
+// (a convex quadratic's minimum over a box is at its centre, or on an edge next to
+// the nearest corner); any point of the box bounds that minimum from above, so the
 // rounding of those positions only costs the second-order loss already covered by
 // t_c.
+__device__ inline bool block_hit(const float4& a0, const float4& a1, float qx, float qy) {
+  const float x0 = a0.x - (qx + 7.0f), x1 = a0.x - qx;
+  const float y0 = a0.y - (qy + 7.0f), y1 = a0.y - qy;
+  // (x0 <= x1 and y0 <= y1: a median of three is a clamp)
+  const float xn = __builtin_amdgcn_fmed3f(0.0f, x0, x1);
+  const float yn = __builtin_amdgcn_fmed3f(0.0f, y0, y1);
+  const float ka = (-0.5f * a0.w) * __builtin_amdgcn_rcpf(a0.z);
+  const float dy1 = __builtin_amdgcn_fmed3f(xn * a1.w, y0, y1);
+  const float dx2 = __builtin_amdgcn_fmed3f(yn * ka, x0, x1);
+  const float f1 = gauss_q(a0.z, a0.w, a1.x, xn, dy1);
+  const float f2 = gauss_q(a0.z, a0.w, a1.x, dx2, yn);
+  return fminf(f1, f2) <= a1.z;
+}
+
+// Ballots of block_hit over the staged records [0, m); bit b of mask[k] is record
+// 64 k + b.
 template <int NM>
 __device__ inline void block_masks(const float4* s0, const float4* s1, int m, float qx, float qy,
                                       uint64_t (&mask)[NM]) {
@@ -177,128 +189,157 @@ __device__ inline void block_masks(const float4* s0, const float4* s1, int m, fl
   for (int k = 0; k < NM; ++k) {
     const int j = lane + 64 * k;
     bool hit = false;
-    if (j < m) {
-      const float4 a0 = s0[j];
-      const float4 a1 = s1[j];
-      const float x0 = a0.x - (qx + 7.0f), x1 = a0.x - qx;
-      const float y0 = a0.y - (qy + 7.0f), y1 = a0.y - qy;
-      // (x0 <= x1 and y0 <= y1: a median of three is a clamp)
-      const float xn = __builtin_amdgcn_fmed3f(0.0f, x0, x1);
-      const float yn = __builtin_amdgcn_fmed3f(0.0f, y0, y1);
-      const float ka = (-0.5f * a0.w) * __builtin_amdgcn_rcpf(a0.z);
-      const float dy1 = __builtin_amdgcn_fmed3f(xn * a1.w, y0, y1);
-      const float dx2 = __builtin_amdgcn_fmed3f(yn * ka, x0, x1);
-      const float f1 = gauss_q(a0.z, a0.w, a1.x, xn, dy1);
-      const float f2 = gauss_q(a0.z, a0.w, a1.x, dx2, yn);
-      hit = fminf(f1, f2) <= a1.z;
-    }
+    if (j < m) hit = block_hit(s0[j], s1[j], qx, qy);
     mask[k] = wave_mask(hit);
   }
 }
 
-// COUNT: the same walk, writing only the number of Gaussians each pixel evaluated up
-// to its termination (those that pass its cutoff test: the blended ones and, if it
-// stopped, the one that stopped it) into evals, and the number of the tile's list
-// entries that at least one of its pixels blended into pairs_eff[tile]; the forward
-// state is left alone.
-template <int T, bool COUNT = false>
-__global__ __launch_bounds__(T * T) void k_render_fwd(const ViewDev* __restrict__ views, int V, int n_tiles_total,
-                                                    const uint2* __restrict__ ranges,
-                                                    const uint32_t* __restrict__ pair_rec,
-                                                    const Record* __restrict__ rec, uint32_t n_rec,
-                                                    float* __restrict__ color,
-                                                    float* __restrict__ t_final, uint32_t* __restrict__ n_contrib,
-                                                    uint32_t* __restrict__ last, float* __restrict__ asum,
-                                                    uint32_t* __restrict__ evals = nullptr,
-                                                    uint32_t* __restrict__ pairs_eff = nullptr) {
-  constexpr int NT = T * T, NM = NT / 64;
-  __shared__ float4 s0[NT], s1[NT], s2[NT];
-  __shared__ uint32_t s_eff[COUNT ? NT / 32 : 1];   // batch entries some pixel blended (COUNT)
-  uint32_t n_eff = 0;
-  const int tile = xcd_raster_tile((int)blockIdx.x);
-  if (tile >= n_tiles_total) return;
-  const TileGeom tg = tile_geom<T>(views, V, tile);
+// x << 1, with the lane's bit of a wave-wide mask shifted in (one add with carry).
+__device__ inline uint32_t shift_in(uint32_t x, uint64_t m) {
+  uint32_t r;
+  asm("v_addc_co_u32_e64 %0, vcc, %1, %1, %2" : "=v"(r) : "v"(x), "s"(m) : "vcc");
+  return r;
+}
+
+// Candidates a wavefront takes together in the forward: their tests and alphas do not
+// depend on each other.  1, 2 or 4 took 692, 657 and 667 us at 1M Gaussians and 10
+// Mpix (six to eight wavefronts per SIMD hide most of it) and 74, 64 and 60 us at 10k
+// Gaussians and 128x128 pixels (256 wavefronts on the whole chip).
+constexpr int kFwdGroup = 4;
+
+// One wavefront per 8x8 block of a tile, four to a workgroup and independent of each
+// other (no barrier: each stops as soon as its own pixels have, and finds the
+// records its neighbours staged in the same caches).  It walks the tile's list 64
+// positions at a time, one record per lane with the next 64 records and the ids of
+// the 64 after them in flight, and writes the records whose cutoff ellipse meets
+// its block to its own LDS rows in list order; every pixel then reads them by LDS
+// broadcast.  Bound by VALU issue: about 55 cycles per candidate and wavefront (a
+// selection of masks held in scalar registers keeps comparisons, selects and scalar
+// operands, four cycles each, to five), 85% of the issue slots taken, where one
+// workgroup per tile with a barrier per batch took 81: 722 -> 667 us at 1M
+// Gaussians, nine views and 10 Mpix, 95 -> 82 us at 300k and 1296x864, 77 -> 60 us at
+// 10k and 128x128.
+template <int T>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k_render_fwd(
+    const ViewDev* __restrict__ views, int V, int n_tiles, const uint2* __restrict__ ranges,
+    const uint32_t* __restrict__ pair_rec, const Record* __restrict__ rec, uint32_t n_rec,
+    float* __restrict__ color, float* __restrict__ t_final, uint32_t* __restrict__ n_contrib,
+    uint32_t* __restrict__ last, float* __restrict__ asum) {
+  constexpr int G = kFwdGroup, QW = T / 8, NBLK = QW * QW, ROWS = 64 + G;
+  __shared__ float4 rows[4][3 * ROWS];
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int lane = (int)__lane_id();
+  const int unit = 4 * xcd_raster_tile((int)blockIdx.x) + wave;
+  const int tile = unit / NBLK, blk = unit % NBLK;
+  if (tile >= n_tiles) return;
+  const int v = view_of_tile(views, V, tile);
+  const ViewDev& cv = views[v];
   const uint2 rg = ranges[tile];
-  const float fx = (float)tg.lx, fy = (float)tg.ly;
-  const float qx = (float)(tg.lx & ~7), qy = (float)(tg.ly & ~7);
+  const int lt = tile - cv.tile_off;
+  const int tx = lt % cv.tiles_x, ty = lt / cv.tiles_x;
+  const int bx = 8 * (blk % QW), by = 8 * (blk / QW);        // block origin in the tile
+  const double ox = (double)(tx * T) + 0.5, oy = (double)(ty * T) + 0.5;
+  const float qx = (float)bx, qy = (float)by;
+  const int px = tx * T + bx + (lane & 7), py = ty * T + by + (lane >> 3);
+  const bool inside = px < cv.W && py < cv.H;
+  const float fx = (float)(bx + (lane & 7)), fy = (float)(by + (lane >> 3));
   float Tr = 1.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f, A = 0.0f;
   uint32_t cnt = 0, lastp = 0;
-  // A pixel takes a Gaussian while its exponent lies in [cutoff, pmax]: pmax is 0
-  // while the pixel blends and -inf once it has stopped (or lies outside the
-  // image), which keeps the test two plain comparisons.
-  float pmax = tg.inside ? 0.0f : -INFINITY;
-  for (uint32_t base = rg.x; base < rg.y; base += NT) {
-    const uint32_t m = min((uint32_t)NT, rg.y - base);
-    __syncthreads();
-    if (COUNT && threadIdx.x < NT / 32) s_eff[threadIdx.x] = 0u;
-    if (threadIdx.x < m) {
-      const uint32_t rid = pair_rec[base + threadIdx.x];
-      if (rid < n_rec) {
-        stage(fetch(rec, rid), tg.ox, tg.oy, s0[threadIdx.x], s1[threadIdx.x], s2[threadIdx.x]);
-      } else {
-        stage_empty(s0[threadIdx.x], s1[threadIdx.x], s2[threadIdx.x]);
-      }
+
+  float4* const r0 = rows[wave];
+  const auto id_at = [&](uint32_t i) {
+    return i + (uint32_t)lane < rg.y ? pair_rec[i + (uint32_t)lane] : ~0u;
+  };
+  uint32_t rid = id_at(rg.x), rid1 = id_at(rg.x + 64u);
+  RawRecord raw{}, raw1{};
+  if (rid < n_rec) raw = fetch(rec, rid);
+  uint64_t live = wave_mask(inside);      // the pixels that have not stopped
+  for (uint32_t base = rg.x; base < rg.y && live != 0ull; base += 64u) {
+    const uint32_t rid2 = id_at(base + 128u);
+    if (rid1 < n_rec) raw1 = fetch(rec, rid1);
+    float4 q0, q1, q2;
+    stage(raw, ox, oy, q0, q1, q2);
+    const bool hit = rid < n_rec && block_hit(q0, q1, qx, qy);
+    const uint64_t mk = wave_mask(hit);
+    const bool caps = wave_mask(hit && q2.x > kAlphaMax) != 0ull;   // some alpha may reach the cap
+    const int n = __popcll(mk);
+    __builtin_amdgcn_wave_barrier();
+    if (hit) {
+      const int r = mask_rank(mk);
+      r0[r] = q0;
+      r0[ROWS + r] = make_float4(q1.x, q1.y, __uint_as_float(base - rg.x + (uint32_t)lane + 1u), 0.0f);
+      r0[2 * ROWS + r] = q2;
     }
-    __syncthreads();
-    if (wave_mask(pmax == 0.0f) != 0ull) {
-      uint64_t mask[NM];
-      block_masks<NM>(s0, s1, (int)m, qx, qy, mask);
-      // straight-line per-Gaussian update; lanes that skip or have stopped keep their state
-      const uint32_t pos0 = base - rg.x + 1;
-      bool live = true;
-      for (int k = 0; k < NM && live; ++k) {
-        uint64_t mk = mask[k];
-        while (mk) {
-          const uint32_t j = 64u * k + (uint32_t)__builtin_ctzll(mk);
-          mk &= mk - 1ull;
-          const float4 a0 = s0[j];
-          const float4 a1 = s1[j];
-          const float dx = a0.x - fx, dy = a0.y - fy;
-          const float q = gauss_q(a0.z, a0.w, a1.x, dx, dy);
-          const bool pass = pmax == 0.0f && passes(q, a1.y);
-          if (wave_mask(pass) != 0ull) {
-            const float4 a2 = s2[j];
-            const float alpha = fminf(kAlphaMax, a2.x * __builtin_amdgcn_exp2f(-q));
-            const float Tn = Tr * (1.0f - alpha);
-            const bool stop = pass && Tn < kTMin;
-            const bool blend = pass && !stop;
-            pmax = stop ? -INFINITY : pmax;
-            const float ab = blend ? alpha : 0.0f;  // this pixel's alpha, 0 if it did not blend
-            const float wgt = ab * Tr;
-            C0 = __fmaf_rn(a2.y, wgt, C0);
-            C1 = __fmaf_rn(a2.z, wgt, C1);
-            C2 = __fmaf_rn(a2.w, wgt, C2);
-            Tr = blend ? Tn : Tr;
-            A += ab;
-            cnt += blend ? 1u : 0u;
-            lastp = blend ? pos0 + j : lastp;
-            if (COUNT && wave_mask(blend) != 0ull && __lane_id() == 0u) atomicOr(&s_eff[j >> 5], 1u << (j & 31u));
-            // leave the batch once every pixel of this wavefront has stopped
-            mk = wave_mask(pmax == 0.0f) == 0ull ? 0ull : mk;
+    if (lane < G) {   // fills up the last group: no pixel accepts it
+      float4 e0, e1, e2;
+      stage_empty(e0, e1, e2);
+      r0[n + lane] = e0;
+      r0[ROWS + n + lane] = e1;
+      r0[2 * ROWS + n + lane] = e2;
+    }
+    __builtin_amdgcn_wave_barrier();
+    // Every step is straight-line over the wavefront; the masks of the pixels that
+    // pass, stop or still blend live in scalar registers.  `hist` collects one bit per
+    // candidate and pixel (blended or not), which gives the count and the last
+    // position once per 32 candidates.
+    const auto walk = [&](auto cap) {
+      constexpr bool CAP = decltype(cap)::value;
+      for (int i0 = 0; i0 < n && live != 0ull; i0 += 32) {
+        uint32_t hist = 0u;
+        int i = i0;
+        for (const int i1 = min(i0 + 32, n); i < i1 && live != 0ull; i += G) {
+          float q[G], al[G];
+          float4 a2[G];
+          uint64_t pass[G];
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            const float4 a0 = r0[i + g];
+            const float2 a1 = *reinterpret_cast<const float2*>(&r0[ROWS + i + g]);
+            a2[g] = r0[2 * ROWS + i + g];
+            // (one 16-byte read here rather than four where its parts are used)
+            asm volatile("" ::"v"(a2[g].x), "v"(a2[g].y), "v"(a2[g].z), "v"(a2[g].w));
+            q[g] = gauss_q(a0.z, a0.w, a1.x, a0.x - fx, a0.y - fy);
+            pass[g] = wave_mask(passes(q[g], a1.y));
+            al[g] = a2[g].x * __builtin_amdgcn_exp2f(-q[g]);
+            if (CAP) al[g] = fminf(kAlphaMax, al[g]);
+            asm volatile("" : "+v"(al[g]));   // (formed here, not in a branch around its use)
+          }
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            uint64_t m = pass[g] & live;
+            float alpha = __builtin_amdgcn_inverse_ballot_w64(m) ? al[g] : 0.0f;   // 0 where it does not blend
+            float Tn = Tr * (1.0f - alpha);
+            const uint64_t stops = wave_mask(Tn < kTMin);
+            if (stops != 0ull) {   // these blend nothing, and nothing more
+              const bool stop = __builtin_amdgcn_inverse_ballot_w64(stops);
+              m &= ~stops;
+              live &= ~stops;
+              alpha = stop ? 0.0f : alpha;
+              Tn = stop ? Tr : Tn;
+            }
+            const float wgt = alpha * Tr;
+            C0 = __fmaf_rn(a2[g].y, wgt, C0);
+            C1 = __fmaf_rn(a2[g].z, wgt, C1);
+            C2 = __fmaf_rn(a2[g].w, wgt, C2);
+            A += alpha;
+            Tr = Tn;
+            hist = shift_in(hist, m);
           }
         }
-        live = wave_mask(pmax == 0.0f) != 0ull;
+        cnt += (uint32_t)__popc(hist);
+        // bit b of hist is row i - 1 - b
+        if (hist != 0u) lastp = __float_as_uint(r0[ROWS + i - __ffs((int)hist)].z);
       }
-    }
-    if (COUNT) {
-      __syncthreads();
-      if (threadIdx.x == 0)
-        for (int w = 0; w < NT / 32; ++w) n_eff += (uint32_t)__popc(s_eff[w]);
-    }
-    if (__syncthreads_and(pmax < 0.0f)) break;
+    };
+    if (caps) walk(std::true_type{});
+    else walk(std::false_type{});
+    raw = raw1;
+    rid = rid1;
+    rid1 = rid2;
   }
-  if (COUNT) {
-    if (tg.inside) {
-      const ViewDev& cv = views[tg.v];
-      evals[(size_t)cv.pix_off + (size_t)tg.py * cv.W + tg.px] = cnt + (pmax < 0.0f ? 1u : 0u);
-    }
-    if (threadIdx.x == 0) pairs_eff[tile] = n_eff;
-    return;
-  }
-  if (tg.inside) {
-    const ViewDev& cv = views[tg.v];
+  if (inside) {
     const size_t hw = (size_t)cv.W * cv.H;
-    const size_t pix = (size_t)tg.py * cv.W + tg.px;
+    const size_t pix = (size_t)py * cv.W + px;
     float* img = color + 3 * (size_t)cv.pix_off;
     img[pix] = C0 + Tr * cv.bg[0];
     img[hw + pix] = C1 + Tr * cv.bg[1];
@@ -309,6 +350,76 @@ __global__ __launch_bounds__(T * T) void k_render_fwd(const ViewDev* __restrict_
     last[gp] = lastp;
     asum[gp] = A;
   }
+}
+
+// The forward's walk, one workgroup of T x T threads per tile (the tile's blocks meet
+// at a barrier per batch of T^2 records, so that they can mark a list entry together),
+// writing the number of Gaussians each pixel evaluates up to its termination (those
+// that pass its cutoff test: the blended ones and, if it stopped, the one that stopped
+// it) into evals, and the number of the tile's list entries that at least one of its
+// pixels blends into pairs_eff[tile].  The same decisions as the forward's: the same
+// staged numbers and the same arithmetic.
+template <int T>
+__global__ __launch_bounds__(T * T) void k_render_count(const ViewDev* __restrict__ views, int V, int n_tiles_total,
+                                                      const uint2* __restrict__ ranges,
+                                                      const uint32_t* __restrict__ pair_rec,
+                                                      const Record* __restrict__ rec, uint32_t n_rec,
+                                                      uint32_t* __restrict__ evals,
+                                                      uint32_t* __restrict__ pairs_eff) {
+  constexpr int NT = T * T, NM = NT / 64;
+  __shared__ float4 s0[NT], s1[NT], s2[NT];
+  __shared__ uint32_t s_eff[NT / 32];   // batch entries some pixel blended
+  uint32_t n_eff = 0;
+  const int tile = xcd_raster_tile((int)blockIdx.x);
+  if (tile >= n_tiles_total) return;
+  const TileGeom tg = tile_geom<T>(views, V, tile);
+  const uint2 rg = ranges[tile];
+  const float fx = (float)tg.lx, fy = (float)tg.ly;
+  const float qx = (float)(tg.lx & ~7), qy = (float)(tg.ly & ~7);
+  float Tr = 1.0f;
+  uint32_t cnt = 0;
+  bool alive = tg.inside;
+  for (uint32_t base = rg.x; base < rg.y; base += NT) {
+    const uint32_t m = min((uint32_t)NT, rg.y - base);
+    __syncthreads();
+    if (threadIdx.x < NT / 32) s_eff[threadIdx.x] = 0u;
+    if (threadIdx.x < m) {
+      const uint32_t rid = pair_rec[base + threadIdx.x];
+      if (rid < n_rec) {
+        stage(fetch(rec, rid), tg.ox, tg.oy, s0[threadIdx.x], s1[threadIdx.x], s2[threadIdx.x]);
+      } else {
+        stage_empty(s0[threadIdx.x], s1[threadIdx.x], s2[threadIdx.x]);
+      }
+    }
+    __syncthreads();
+    uint64_t mask[NM];
+    block_masks<NM>(s0, s1, (int)m, qx, qy, mask);
+    for (int k = 0; k < NM; ++k) {
+      for (uint64_t mk = mask[k]; mk != 0ull && wave_mask(alive) != 0ull; mk &= mk - 1ull) {
+        const uint32_t j = 64u * k + (uint32_t)__builtin_ctzll(mk);
+        const float4 a0 = s0[j];
+        const float4 a1 = s1[j];
+        const float q = gauss_q(a0.z, a0.w, a1.x, a0.x - fx, a0.y - fy);
+        const bool pass = alive & passes(q, a1.y);
+        const float alpha = fminf(kAlphaMax, s2[j].x * __builtin_amdgcn_exp2f(-q));
+        const float Tn = Tr * (1.0f - alpha);
+        const bool blend = pass && !(Tn < kTMin);
+        cnt += pass ? 1u : 0u;
+        alive = alive && !(pass && Tn < kTMin);
+        Tr = blend ? Tn : Tr;
+        if (wave_mask(blend) != 0ull && __lane_id() == 0u) atomicOr(&s_eff[j >> 5], 1u << (j & 31u));
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+      for (int w = 0; w < NT / 32; ++w) n_eff += (uint32_t)__popc(s_eff[w]);
+    if (__syncthreads_and(!alive)) break;
+  }
+  if (tg.inside) {
+    const ViewDev& cv = views[tg.v];
+    evals[(size_t)cv.pix_off + (size_t)tg.py * cv.W + tg.px] = cnt;
+  }
+  if (threadIdx.x == 0) pairs_eff[tile] = n_eff;
 }
 
 // Lane l receives v from the lane the DPP control names (row_half_mirror = 0x141:
@@ -658,22 +769,19 @@ hipError_t launch_render_fwd(const ViewDev* views, int V, int n_tiles, const uin
                              const Record* rec, uint32_t n_rec, float* color, float* t_final, uint32_t* n_contrib,
                              uint32_t* last, float* asum, int tile, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
-  const dim3 grid((unsigned)((n_tiles + 8 * kXcdRun - 1) / (8 * kXcdRun) * (8 * kXcdRun)));
+  // four 8x8 blocks to a workgroup
+  const int64_t groups = ((int64_t)n_tiles * (tile / 8) * (tile / 8) + 3) / 4, round = 8 * kXcdRun;
+  const dim3 grid((unsigned)((groups + round - 1) / round * round));
+#define GS_FWD(TT)                                                                                                  \
+  hipLaunchKernelGGL(k_render_fwd<TT>, grid, dim3(256), 0, s, views, V, n_tiles, ranges, pair_rec, rec, n_rec, color, \
+                     t_final, n_contrib, last, asum)
   switch (tile) {
-    case 8:
-      hipLaunchKernelGGL(k_render_fwd<8>, grid, dim3(64), 0, s, views, V, n_tiles, ranges, pair_rec, rec, n_rec, color, t_final,
-                         n_contrib, last, asum);
-      break;
-    case 16:
-      hipLaunchKernelGGL(k_render_fwd<16>, grid, dim3(256), 0, s, views, V, n_tiles, ranges, pair_rec, rec, n_rec, color,
-                         t_final, n_contrib, last, asum);
-      break;
-    case 32:
-      hipLaunchKernelGGL(k_render_fwd<32>, grid, dim3(1024), 0, s, views, V, n_tiles, ranges, pair_rec, rec, n_rec, color,
-                         t_final, n_contrib, last, asum);
-      break;
+    case 8: GS_FWD(8); break;
+    case 16: GS_FWD(16); break;
+    case 32: GS_FWD(32); break;
     default: return hipErrorInvalidValue;
   }
+#undef GS_FWD
   return hipGetLastError();
 }
 
@@ -682,21 +790,16 @@ hipError_t launch_render_count(const ViewDev* views, int V, int n_tiles, const u
                                hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
   const dim3 grid((unsigned)((n_tiles + 8 * kXcdRun - 1) / (8 * kXcdRun) * (8 * kXcdRun)));
+#define GS_COUNT(TT)                                                                                                  \
+  hipLaunchKernelGGL(k_render_count<TT>, grid, dim3(TT * TT), 0, s, views, V, n_tiles, ranges, pair_rec, rec, n_rec, \
+                     evals, pairs_eff)
   switch (tile) {
-    case 8:
-      hipLaunchKernelGGL((k_render_fwd<8, true>), grid, dim3(64), 0, s, views, V, n_tiles, ranges, pair_rec, rec, n_rec,
-                         nullptr, nullptr, nullptr, nullptr, nullptr, evals, pairs_eff);
-      break;
-    case 16:
-      hipLaunchKernelGGL((k_render_fwd<16, true>), grid, dim3(256), 0, s, views, V, n_tiles, ranges, pair_rec, rec,
-                         n_rec, nullptr, nullptr, nullptr, nullptr, nullptr, evals, pairs_eff);
-      break;
-    case 32:
-      hipLaunchKernelGGL((k_render_fwd<32, true>), grid, dim3(1024), 0, s, views, V, n_tiles, ranges, pair_rec, rec,
-                         n_rec, nullptr, nullptr, nullptr, nullptr, nullptr, evals, pairs_eff);
-      break;
+    case 8: GS_COUNT(8); break;
+    case 16: GS_COUNT(16); break;
+    case 32: GS_COUNT(32); break;
     default: return hipErrorInvalidValue;
   }
+#undef GS_COUNT
   return hipGetLastError();
 }
 
