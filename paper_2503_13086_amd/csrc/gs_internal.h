@@ -398,10 +398,22 @@ __device__ inline float adam_view_factor(const AdamArgs& a, const uint32_t* touc
   return c > 0 ? s / (float)c : all / (float)a.n_views;
 }
 
-// Bias corrections 1 - b^k for step k (k = the element's updated step counter).
+// Bias corrections 1 - b^k for step k (k = the element's updated step counter), the
+// powers by squaring in FP64: their relative error is below k 2^-52, and b^k vanishes
+// long before that reaches half an ulp of the fp32 result.  (pow() costs five times as
+// many instructions and 60 registers more.)
 __device__ inline void adam_bias(const AdamArgs& a, uint32_t k, float& bc1, float& bc2) {
-  bc1 = (float)(1.0 - pow((double)a.b1, (double)k));
-  bc2 = (float)(1.0 - pow((double)a.b2, (double)k));
+  double p1 = 1.0, p2 = 1.0, q1 = (double)a.b1, q2 = (double)a.b2;
+  for (uint32_t e = k; e != 0u; e >>= 1) {
+    if (e & 1u) {
+      p1 *= q1;
+      p2 *= q2;
+    }
+    q1 *= q1;
+    q2 *= q2;
+  }
+  bc1 = (float)(1.0 - p1);
+  bc2 = (float)(1.0 - p2);
 }
 
 // One element: m = b1 m + (1 - b1) g, v = b2 v + (1 - b2) g^2,

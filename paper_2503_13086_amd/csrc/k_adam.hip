@@ -12,6 +12,8 @@
 namespace gsk {
 namespace {
 
+constexpr int kGroup = 4;   // rows whose loads are in flight together
+
 __global__ __launch_bounds__(256) void k_adam(float* __restrict__ P, const float* __restrict__ G,
                                                float* __restrict__ M, float* __restrict__ Vv,
                                                uint32_t* __restrict__ step, int n, int stride, int rows, AdamArgs a,
@@ -25,15 +27,31 @@ __global__ __launch_bounds__(256) void k_adam(float* __restrict__ P, const float
   float bc1, bc2;
   adam_bias(a, k, bc1, bc2);
   const float factor = adam_view_factor(a, touched, n, g);
-  for (int r = 0; r < rows; ++r) {
-    const int grp = adam_row_group(r);
-    const float lr = ((a.group_mask >> grp) & 1u) ? a.lr[grp] * factor : a.lr[grp];
-    const size_t i = (size_t)r * stride + g;
-    float p = P[i], m = M[i], v = Vv[i];
-    adam_elem(p, m, v, G[i], lr, a, bc1, bc2);
-    M[i] = m;
-    Vv[i] = v;
-    P[i] = p;
+  for (int r0 = 0; r0 < rows; r0 += kGroup) {
+    float p[kGroup], m[kGroup], v[kGroup], gr[kGroup];
+#pragma unroll
+    for (int j = 0; j < kGroup; ++j) {
+      if (r0 + j < rows) {
+        const size_t i = (size_t)(r0 + j) * stride + g;
+        p[j] = P[i];
+        gr[j] = G[i];
+        m[j] = __builtin_nontemporal_load(M + i);
+        v[j] = __builtin_nontemporal_load(Vv + i);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < kGroup; ++j) {
+      const int r = r0 + j;
+      if (r < rows) {
+        const int grp = adam_row_group(r);
+        const float lr = ((a.group_mask >> grp) & 1u) ? a.lr[grp] * factor : a.lr[grp];
+        const size_t i = (size_t)r * stride + g;
+        adam_elem(p[j], m[j], v[j], gr[j], lr, a, bc1, bc2);
+        __builtin_nontemporal_store(m[j], M + i);
+        __builtin_nontemporal_store(v[j], Vv + i);
+        P[i] = p[j];
+      }
+    }
   }
 }
 

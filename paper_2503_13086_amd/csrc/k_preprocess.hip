@@ -18,6 +18,8 @@
 // (u, w, a, b, c, o, rgb) to mean, covariance, opacity and SH coefficients, sums
 // the views, takes covariance to log-scale and quaternion in FP64 once, and
 // writes each gradient once.
+#include <type_traits>
+
 #include "gs_geom.h"
 
 #pragma clang fp contract(off)
@@ -208,184 +210,139 @@ __device__ inline void load_grad2d(const float* __restrict__ src, uint32_t touch
   }
 }
 
-// With adam != 0 the gradient is applied at once (params updated in place, `out`
-// written only when not NULL); otherwise it goes to `out` (or is added to it).
-// One kernel serves both so that the gradient is the same machine arithmetic
-// either way.  The parameters are read before this thread writes any of them,
-// and a thread touches only its own Gaussian's column.
+// Colour part of one view: dL/d(raw colour) and the basis, whose products are the SH
+// coefficients' gradients, and the mean's gradient through the view direction.
 template <int D>
-__global__ __launch_bounds__(256) void k_preprocess_bwd(float* P, int n, int stride,
-                                                         const ViewDev* __restrict__ views, int V,
-                                                         const uint32_t* __restrict__ touched,
-                                                         const float* __restrict__ grad2d, float* out,
-                                                         int accumulate, int adam, float* M, float* Vv,
-                                                         uint32_t* step, AdamArgs a, const DevStatus* st) {
+__device__ inline void colour_grad(const ViewDev& cv, const GaussF& G, const float (&f)[3 * (D + 1) * (D + 1)],
+                                   const float (&grgb)[3], float (&graw)[3], float (&Y)[16], float (&gm)[3]) {
 #pragma clang fp contract(fast)
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= n) return;
-  if (adam && st && st->code != GS_OK) return;   // the binning of this step failed: leave the state
   constexpr int K = (D + 1) * (D + 1);
-  // the loads of the view loop run ahead of it: the touched flag of view v + 2 and
-  // the 2D gradient of view v + 1 are in flight while view v is processed (at two
-  // waves per SIMD nothing else would cover their latency)
-  uint32_t t_next = V > 0 ? touched[g] : 0u;                  // view v + 1
-  uint32_t t_after = V > 1 ? touched[(size_t)n + g] : 0u;     // view v + 2
-  const uint32_t step_old = adam ? step[g] : 0u;
-  GaussF G;
-  gauss_geom_f(P, stride, g, G);
-
-  float gm[3] = {0.f, 0.f, 0.f};       // dL/dmean
-  float gSig[3][3] = {{0.f}};          // symmetric dL/dSigma accumulated over views
-  float go = 0.f;                      // dL/dopacity
-  float gf[3 * K];                     // dL/dSH
-  float f[3 * K];                      // SH coefficients, held across the views
+  float Wr[3][3];
+  for (int i = 0; i < 3; ++i)
+    for (int j = 0; j < 3; ++j) Wr[i][j] = cv.R[3 * i + j];
+  // colour: raw = 1/2 + sum_k f_k Y_k(dir), clamped at 0 (zero derivative when
+  // clamped); dir from the camera centre -W^T t to the mean
+  float oc[3];
+  for (int k = 0; k < 3; ++k) oc[k] = -(Wr[0][k] * cv.t[0] + Wr[1][k] * cv.t[1] + Wr[2][k] * cv.t[2]);
+  const float d0 = G.m[0] - oc[0], d1 = G.m[1] - oc[1], d2 = G.m[2] - oc[2];
+  const float dn = sqrtf(d0 * d0 + d1 * d1 + d2 * d2);
+  const float dir[3] = {d0 / dn, d1 / dn, d2 / dn};
+  sh_eval<float>(D, dir[0], dir[1], dir[2], Y);
 #pragma unroll
-  for (int i = 0; i < 3 * K; ++i) {
-    gf[i] = 0.f;
-    f[i] = P[(size_t)(11 + i) * stride + g];
+  for (int ch = 0; ch < 3; ++ch) {
+    float acc = 0.5f;
+#pragma unroll
+    for (int k = 0; k < K; ++k) acc += f[3 * k + ch] * Y[k];
+    graw[ch] = acc < 0.0f ? 0.0f : grgb[ch];
   }
-
-  // the per-view learning-rate factor of the fused step (the mean of the scales of
-  // the views that see the Gaussian, else of all), summed in view order as
-  // adam_view_factor does, from the flags the loop reads anyway
-  const bool fold_factor = adam && a.n_views == V;
-  float fs = 0.0f, fall = 0.0f;
-  int fc = 0;
-  float g2n[kGrad2D];
-  load_grad2d(grad2d + (size_t)g * kGrad2D, t_next, g2n);
-  for (int v = 0; v < V; ++v) {
-    const uint32_t t_cur = t_next;
-    float g2[kGrad2D];
+  float gY[16];
 #pragma unroll
-    for (int k = 0; k < kGrad2D; ++k) g2[k] = g2n[k];
-    t_next = t_after;
-    if (v + 1 < V) load_grad2d(grad2d + ((size_t)(v + 1) * n + g) * kGrad2D, t_next, g2n);
-    t_after = v + 2 < V ? touched[(size_t)(v + 2) * n + g] : 0u;
-    if (fold_factor) {
-      fall += a.scale[v];
-      if (t_cur != 0u) {
-        fs += a.scale[v];
-        ++fc;
-      }
-    }
-    if (t_cur == 0u) continue;
-    const ViewDev& cv = views[v];
-    const float gu = g2[0], gw = g2[1], ga = g2[2], gb = g2[3], gc = g2[4];
-    go += g2[5];
-    const float grgb[3] = {g2[6], g2[7], g2[8]};
-    float Wr[3][3];
-    for (int i = 0; i < 3; ++i)
-      for (int j = 0; j < 3; ++j) Wr[i][j] = cv.R[3 * i + j];
-
-    // colour: raw = 1/2 + sum_k f_k Y_k(dir), clamped at 0 (zero derivative when
-    // clamped); dir from the camera centre -W^T t to the mean
-    float oc[3];
-    for (int k = 0; k < 3; ++k) oc[k] = -(Wr[0][k] * cv.t[0] + Wr[1][k] * cv.t[1] + Wr[2][k] * cv.t[2]);
-    const float d0 = G.m[0] - oc[0], d1 = G.m[1] - oc[1], d2 = G.m[2] - oc[2];
-    const float dn = sqrtf(d0 * d0 + d1 * d1 + d2 * d2);
-    const float dir[3] = {d0 / dn, d1 / dn, d2 / dn};
-    float Y[16];
-    sh_eval<float>(D, dir[0], dir[1], dir[2], Y);
-    float graw[3];
+  for (int k = 0; k < K; ++k) {
+    gY[k] = 0.0f;
 #pragma unroll
     for (int ch = 0; ch < 3; ++ch) {
-      float acc = 0.5f;
-#pragma unroll
-      for (int k = 0; k < K; ++k) acc += f[3 * k + ch] * Y[k];
-      graw[ch] = acc < 0.0f ? 0.0f : grgb[ch];
+      gY[k] += graw[ch] * f[3 * k + ch];
     }
-    float gY[16];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      gY[k] = 0.0f;
-#pragma unroll
-      for (int ch = 0; ch < 3; ++ch) {
-        gf[3 * k + ch] += graw[ch] * Y[k];
-        gY[k] += graw[ch] * f[3 * k + ch];
-      }
-    }
-    float gdir[3];
-    sh_grad_dir(D, dir[0], dir[1], dir[2], gY, gdir);
-    const float dd = gdir[0] * dir[0] + gdir[1] * dir[1] + gdir[2] * dir[2];
-    for (int k = 0; k < 3; ++k) gm[k] += (gdir[k] - dir[k] * dd) / dn;
-
-    // projection (the forward's formulas; the clamp state is re-derived)
-    const float tx = Wr[0][0] * G.m[0] + Wr[0][1] * G.m[1] + Wr[0][2] * G.m[2] + cv.t[0];
-    const float ty = Wr[1][0] * G.m[0] + Wr[1][1] * G.m[1] + Wr[1][2] * G.m[2] + cv.t[1];
-    const float tz = Wr[2][0] * G.m[0] + Wr[2][1] * G.m[1] + Wr[2][2] * G.m[2] + cv.t[2];
-    const float fx = cv.fx, fy = cv.fy;
-    const float limx = ((float)kJacClamp * (0.5f * (float)cv.W)) / fx;
-    const float limy = ((float)kJacClamp * (0.5f * (float)cv.H)) / fy;
-    const float rx = tx / tz, ry = ty / tz;
-    const bool clx = !(rx >= -limx && rx <= limx), cly = !(ry >= -limy && ry <= limy);
-    const float txc = tz * fminf(fmaxf(rx, -limx), limx), tyc = tz * fminf(fmaxf(ry, -limy), limy);
-    const float J00 = fx / tz, J02 = -(fx * txc) / (tz * tz);
-    const float J11 = fy / tz, J12 = -(fy * tyc) / (tz * tz);
-    float T0[3], T1[3];
-    for (int k = 0; k < 3; ++k) {
-      T0[k] = J00 * Wr[0][k] + J02 * Wr[2][k];
-      T1[k] = J11 * Wr[1][k] + J12 * Wr[2][k];
-    }
-    float ST0[3], ST1[3];
-    for (int k = 0; k < 3; ++k) {
-      ST0[k] = G.Sig[k][0] * T0[0] + G.Sig[k][1] * T0[1] + G.Sig[k][2] * T0[2];
-      ST1[k] = G.Sig[k][0] * T1[0] + G.Sig[k][1] * T1[1] + G.Sig[k][2] * T1[2];
-    }
-    const float S00 = ST0[0] * T0[0] + ST0[1] * T0[1] + ST0[2] * T0[2] + (float)kKappa;
-    const float S01 = ST0[0] * T1[0] + ST0[1] * T1[1] + ST0[2] * T1[2];
-    const float S11 = ST1[0] * T1[0] + ST1[1] * T1[1] + ST1[2] * T1[2] + (float)kKappa;
-    const float idet = 1.0f / (S00 * S11 - S01 * S01);
-    const float A00 = S11 * idet, A01 = -S01 * idet, A11 = S00 * idet;
-
-    // conic (a, b, c) = inverse of S -> dL/dS = -A Gc A, Gc = [[ga, gb/2], [gb/2, gc]]
-    const float H00 = ga * A00 + 0.5f * gb * A01, H01 = ga * A01 + 0.5f * gb * A11;
-    const float H10 = 0.5f * gb * A00 + gc * A01, H11 = 0.5f * gb * A01 + gc * A11;  // Gc A
-    const float gS00 = -(A00 * H00 + A01 * H10);
-    const float gS11 = -(A01 * H01 + A11 * H11);
-    const float gS01 = -2.0f * (A00 * H01 + A01 * H11);   // S01 appears in both off-diagonal slots
-
-    // S = T Sigma T^T (+ kappa I): dL/dSigma (symmetric part) and dL/dT
-    for (int k = 0; k < 3; ++k)
-      for (int l = 0; l < 3; ++l)
-        gSig[k][l] += gS00 * T0[k] * T0[l] + 0.5f * gS01 * (T0[k] * T1[l] + T1[k] * T0[l]) + gS11 * T1[k] * T1[l];
-    float gT0[3], gT1[3];
-    for (int k = 0; k < 3; ++k) {
-      gT0[k] = 2.0f * gS00 * ST0[k] + gS01 * ST1[k];
-      gT1[k] = gS01 * ST0[k] + 2.0f * gS11 * ST1[k];
-    }
-    // T0 = J00 W0 + J02 W2, T1 = J11 W1 + J12 W2 (W = view rotation rows)
-    float gJ00 = 0.f, gJ02 = 0.f, gJ11 = 0.f, gJ12 = 0.f;
-    for (int k = 0; k < 3; ++k) {
-      gJ00 += gT0[k] * Wr[0][k];
-      gJ02 += gT0[k] * Wr[2][k];
-      gJ11 += gT1[k] * Wr[1][k];
-      gJ12 += gT1[k] * Wr[2][k];
-    }
-    const float tz2 = tz * tz, tz3 = tz2 * tz;
-    float gt[3] = {0.f, 0.f, 0.f};
-    // u = fx tx / tz + cx, w = fy ty / tz + cy
-    gt[0] += gu * fx / tz;
-    gt[1] += gw * fy / tz;
-    gt[2] += -(gu * fx * tx + gw * fy * ty) / tz2;
-    // J00 = fx / tz, J11 = fy / tz
-    gt[2] += -(gJ00 * fx + gJ11 * fy) / tz2;
-    // J02 = -fx txc / tz^2 with txc = tx (free) or tz * (+-lim) (clamped)
-    if (!clx) {
-      gt[0] += -gJ02 * fx / tz2;
-      gt[2] += gJ02 * 2.0f * fx * txc / tz3;
-    } else {
-      gt[2] += gJ02 * fx * txc / tz3;
-    }
-    if (!cly) {
-      gt[1] += -gJ12 * fy / tz2;
-      gt[2] += gJ12 * 2.0f * fy * tyc / tz3;
-    } else {
-      gt[2] += gJ12 * fy * tyc / tz3;
-    }
-    // t = W mean + t_v
-    for (int k = 0; k < 3; ++k) gm[k] += Wr[0][k] * gt[0] + Wr[1][k] * gt[1] + Wr[2][k] * gt[2];
   }
+  float gdir[3];
+  sh_grad_dir(D, dir[0], dir[1], dir[2], gY, gdir);
+  const float dd = gdir[0] * dir[0] + gdir[1] * dir[1] + gdir[2] * dir[2];
+  for (int k = 0; k < 3; ++k) gm[k] += (gdir[k] - dir[k] * dd) / dn;
 
+}
+
+// Projection and covariance part of one view: the mean's gradient and the symmetric
+// dL/dSigma from dL/d(u, w, a, b, c) = g2[0..4].
+__device__ inline void geom_grad(const ViewDev& cv, const GaussF& G, const float (&g2)[kGrad2D], float (&gm)[3],
+                                 float (&gSig)[3][3]) {
+#pragma clang fp contract(fast)
+  const float gu = g2[0], gw = g2[1], ga = g2[2], gb = g2[3], gc = g2[4];
+  float Wr[3][3];
+  for (int i = 0; i < 3; ++i)
+    for (int j = 0; j < 3; ++j) Wr[i][j] = cv.R[3 * i + j];
+  // projection (the forward's formulas; the clamp state is re-derived)
+  const float tx = Wr[0][0] * G.m[0] + Wr[0][1] * G.m[1] + Wr[0][2] * G.m[2] + cv.t[0];
+  const float ty = Wr[1][0] * G.m[0] + Wr[1][1] * G.m[1] + Wr[1][2] * G.m[2] + cv.t[1];
+  const float tz = Wr[2][0] * G.m[0] + Wr[2][1] * G.m[1] + Wr[2][2] * G.m[2] + cv.t[2];
+  const float fx = cv.fx, fy = cv.fy;
+  const float limx = ((float)kJacClamp * (0.5f * (float)cv.W)) / fx;
+  const float limy = ((float)kJacClamp * (0.5f * (float)cv.H)) / fy;
+  const float rx = tx / tz, ry = ty / tz;
+  const bool clx = !(rx >= -limx && rx <= limx), cly = !(ry >= -limy && ry <= limy);
+  const float txc = tz * fminf(fmaxf(rx, -limx), limx), tyc = tz * fminf(fmaxf(ry, -limy), limy);
+  const float J00 = fx / tz, J02 = -(fx * txc) / (tz * tz);
+  const float J11 = fy / tz, J12 = -(fy * tyc) / (tz * tz);
+  float T0[3], T1[3];
+  for (int k = 0; k < 3; ++k) {
+    T0[k] = J00 * Wr[0][k] + J02 * Wr[2][k];
+    T1[k] = J11 * Wr[1][k] + J12 * Wr[2][k];
+  }
+  float ST0[3], ST1[3];
+  for (int k = 0; k < 3; ++k) {
+    ST0[k] = G.Sig[k][0] * T0[0] + G.Sig[k][1] * T0[1] + G.Sig[k][2] * T0[2];
+    ST1[k] = G.Sig[k][0] * T1[0] + G.Sig[k][1] * T1[1] + G.Sig[k][2] * T1[2];
+  }
+  const float S00 = ST0[0] * T0[0] + ST0[1] * T0[1] + ST0[2] * T0[2] + (float)kKappa;
+  const float S01 = ST0[0] * T1[0] + ST0[1] * T1[1] + ST0[2] * T1[2];
+  const float S11 = ST1[0] * T1[0] + ST1[1] * T1[1] + ST1[2] * T1[2] + (float)kKappa;
+  // (FP64: the difference cancels for long thin splats, and costs nothing measurable)
+  const float idet = (float)(1.0 / ((double)S00 * S11 - (double)S01 * S01));
+  const float A00 = S11 * idet, A01 = -S01 * idet, A11 = S00 * idet;
+
+  // conic (a, b, c) = inverse of S -> dL/dS = -A Gc A, Gc = [[ga, gb/2], [gb/2, gc]]
+  const float H00 = ga * A00 + 0.5f * gb * A01, H01 = ga * A01 + 0.5f * gb * A11;
+  const float H10 = 0.5f * gb * A00 + gc * A01, H11 = 0.5f * gb * A01 + gc * A11;  // Gc A
+  const float gS00 = -(A00 * H00 + A01 * H10);
+  const float gS11 = -(A01 * H01 + A11 * H11);
+  const float gS01 = -2.0f * (A00 * H01 + A01 * H11);   // S01 appears in both off-diagonal slots
+
+  // S = T Sigma T^T (+ kappa I): dL/dSigma (symmetric part) and dL/dT
+  for (int k = 0; k < 3; ++k)
+    for (int l = 0; l < 3; ++l)
+      gSig[k][l] += gS00 * T0[k] * T0[l] + 0.5f * gS01 * (T0[k] * T1[l] + T1[k] * T0[l]) + gS11 * T1[k] * T1[l];
+  float gT0[3], gT1[3];
+  for (int k = 0; k < 3; ++k) {
+    gT0[k] = 2.0f * gS00 * ST0[k] + gS01 * ST1[k];
+    gT1[k] = gS01 * ST0[k] + 2.0f * gS11 * ST1[k];
+  }
+  // T0 = J00 W0 + J02 W2, T1 = J11 W1 + J12 W2 (W = view rotation rows)
+  float gJ00 = 0.f, gJ02 = 0.f, gJ11 = 0.f, gJ12 = 0.f;
+  for (int k = 0; k < 3; ++k) {
+    gJ00 += gT0[k] * Wr[0][k];
+    gJ02 += gT0[k] * Wr[2][k];
+    gJ11 += gT1[k] * Wr[1][k];
+    gJ12 += gT1[k] * Wr[2][k];
+  }
+  const float tz2 = tz * tz, tz3 = tz2 * tz;
+  float gt[3] = {0.f, 0.f, 0.f};
+  // u = fx tx / tz + cx, w = fy ty / tz + cy
+  gt[0] += gu * fx / tz;
+  gt[1] += gw * fy / tz;
+  gt[2] += -(gu * fx * tx + gw * fy * ty) / tz2;
+  // J00 = fx / tz, J11 = fy / tz
+  gt[2] += -(gJ00 * fx + gJ11 * fy) / tz2;
+  // J02 = -fx txc / tz^2 with txc = tx (free) or tz * (+-lim) (clamped)
+  if (!clx) {
+    gt[0] += -gJ02 * fx / tz2;
+    gt[2] += gJ02 * 2.0f * fx * txc / tz3;
+  } else {
+    gt[2] += gJ02 * fx * txc / tz3;
+  }
+  if (!cly) {
+    gt[1] += -gJ12 * fy / tz2;
+    gt[2] += gJ12 * 2.0f * fy * tyc / tz3;
+  } else {
+    gt[2] += gJ12 * fy * tyc / tz3;
+  }
+  // t = W mean + t_v
+  for (int k = 0; k < 3; ++k) gm[k] += Wr[0][k] * gt[0] + Wr[1][k] * gt[1] + Wr[2][k] * gt[2];
+}
+
+// The gradients of the eleven rows before the SH coefficients (log-scale, quaternion
+// and opacity through their activations), FP64, once per Gaussian.
+__device__ inline void finish_geom(const float* P, int stride, int g, const float (&gSig)[3][3], const float (&gm)[3],
+                                   float go, float (&out)[11]) {
+#pragma clang fp contract(fast)
   // Sigma = M M^T -> dL/dM = 2 sym(dL/dSigma) M; M = Rq diag(s); then the
   // activations (FP64, once per Gaussian)
   Gauss H;
@@ -415,74 +372,226 @@ __global__ __launch_bounds__(256) void k_preprocess_bwd(float* P, int n, int str
   for (int k = 0; k < 3; ++k) outv[3 + k] = gs[k] * H.s[k];
   for (int k = 0; k < 4; ++k) outv[6 + k] = (gq[k] - H.q[k] * qd) / H.qn;
   outv[10] = (double)go * H.o * (1.0 - H.o);
-  if (adam) {
-    const uint32_t k = step_old + 1u;
-    step[g] = k;
-    float bc1, bc2;
-    adam_bias(a, k, bc1, bc2);
-    const float factor = fold_factor ? (fc > 0 ? fs / (float)fc : fall / (float)a.n_views)
-                                     : adam_view_factor(a, touched, n, g);
-    constexpr int ROWS = 11 + 3 * K, B = 8;
-    float grv[ROWS];
+  for (int r = 0; r < 11; ++r) out[r] = (float)outv[r];
+}
+
+// With adam != 0 the gradient is applied at once (params updated in place, `out`
+// written only when not NULL); otherwise it goes to `out` (or is added to it).
+// One kernel serves both so that the gradient is the same machine arithmetic
+// either way.  The parameters are read before this thread writes any of them,
+// and a thread touches only its own Gaussian's column.
+// What a backward kernel does with the gradient it forms.  kBwdAdamBig: the parameters
+// are written past the caches (apply_rows).
+enum BwdOut { kBwdStore, kBwdAccumulate, kBwdAdam, kBwdAdamStore, kBwdAdamBig };
+
+constexpr int kRowGroup = 4;   // rows whose loads are in flight (6: 5 % slower with many views, 8 spills)
+
+// Stores the gradient of every row, adds it to what is there, or applies it at once
+// (fused step).  f holds the SH rows of P.  The kernels share this function, so the
+// gradient is the same machine arithmetic either way.
+// The fused step is bound by HBM: every row of P, M and V read and written once.  Rows
+// go in groups of kRowGroup, the loads of the next group issued before this group's
+// arithmetic and stores (rows of one thread never alias: each group's loads precede its
+// own stores, and no group reads another's rows).  M and V bypass the caches, nothing
+// reads them before the next step; P's stores do so where P outgrows the last-level
+// cache anyway (kBwdAdamBig): 3 000 000 Gaussians of degree 3 in one view take 963 us
+// with cached accesses, 880 with M and V past the caches and 846 with P's stores too
+// (5.2 TB/s, what a bare copy of 177 rows at once reaches); but 300 000, whose P stays
+// in the cache for the next forward, 80 and 82, and the forward then 2 more.
+template <int D, BwdOut OUT, typename GradOf>
+__device__ inline void apply_rows(float* P, int stride, int g0, uint32_t step_new, float* out, float* M, float* Vv,
+                                  const AdamArgs& a, float factor, const float (&f)[3 * (D + 1) * (D + 1)],
+                                  const GradOf& grad_of) {
+  constexpr int ROWS = 11 + 3 * (D + 1) * (D + 1), B = kRowGroup;
+  // element of row r of this thread: a scalar base and a 32-bit lane offset
+  uint32_t lane4 = threadIdx.x * 4u;
+  asm volatile("" : "+v"(lane4));   // (the addresses are formed anew, not held since the first loads)
+  const auto at = [&](float* base, int r) -> float& {
+    return *reinterpret_cast<float*>(reinterpret_cast<char*>(base + (size_t)r * stride + g0) + lane4);
+  };
+  if (OUT == kBwdStore || OUT == kBwdAccumulate) {
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r) grv[r] = r < 11 ? (float)outv[r] : gf[r - 11];
-    // rows in groups of B, the loads of the next group issued before this group's
-    // arithmetic and stores (rows of one thread never alias: each group's loads
-    // precede its own stores, and no group reads another's rows)
-    float np[B], nm[B], nv[B];
-#pragma unroll
-    for (int j = 0; j < B; ++j) {
-      if (j < ROWS) {
-        const size_t i = (size_t)j * stride + g;
-        np[j] = P[i];
-        nm[j] = M[i];
-        nv[j] = Vv[i];
-      }
-    }
-#pragma unroll
-    for (int r0 = 0; r0 < ROWS; r0 += B) {
-      float pp[B], mm[B], vv[B];
-#pragma unroll
-      for (int j = 0; j < B; ++j) {
-        pp[j] = np[j];
-        mm[j] = nm[j];
-        vv[j] = nv[j];
-      }
-#pragma unroll
-      for (int j = 0; j < B; ++j) {
-        if (r0 + B + j < ROWS) {
-          const size_t i = (size_t)(r0 + B + j) * stride + g;
-          np[j] = P[i];
-          nm[j] = M[i];
-          nv[j] = Vv[i];
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < B; ++j) {
-        const int r = r0 + j;
-        if (r < ROWS) {
-          const int grp = adam_row_group(r);
-          const float lr = ((a.group_mask >> grp) & 1u) ? a.lr[grp] * factor : a.lr[grp];
-          adam_elem(pp[j], mm[j], vv[j], grv[r], lr, a, bc1, bc2);
-          const size_t i = (size_t)r * stride + g;
-          if (out) out[i] = grv[r];
-          P[i] = pp[j];
-          M[i] = mm[j];
-          Vv[i] = vv[j];
-        }
-      }
+    for (int r = 0; r < ROWS; ++r) {
+#pragma clang fp contract(off)
+      at(out, r) = OUT == kBwdAccumulate ? at(out, r) + grad_of(r) : grad_of(r);
     }
     return;
   }
-  for (int r = 0; r < 11; ++r) {
-    float* dst = out + (size_t)r * stride + g;
-    *dst = accumulate ? *dst + (float)outv[r] : (float)outv[r];
+  float bc1, bc2;
+  adam_bias(a, step_new, bc1, bc2);
+  float np[B], nm[B], nv[B];
+  const auto load = [&](int j, int r) {
+    np[j] = r < 11 ? at(P, r) : f[r < 11 ? 0 : r - 11];
+    nm[j] = __builtin_nontemporal_load(&at(M, r));
+    nv[j] = __builtin_nontemporal_load(&at(Vv, r));
+  };
+#pragma unroll
+  for (int j = 0; j < B; ++j) load(j, j);
+#pragma unroll
+  for (int r0 = 0; r0 < ROWS; r0 += B) {
+    float pp[B], mm[B], vv[B];
+#pragma unroll
+    for (int j = 0; j < B; ++j) {
+      pp[j] = np[j];
+      mm[j] = nm[j];
+      vv[j] = nv[j];
+    }
+#pragma unroll
+    for (int j = 0; j < B; ++j)
+      if (r0 + B + j < ROWS) load(j, r0 + B + j);
+#pragma unroll
+    for (int j = 0; j < B; ++j) {
+      const int r = r0 + j;
+      if (r < ROWS) {
+        const int grp = adam_row_group(r);
+        const float lr = ((a.group_mask >> grp) & 1u) ? a.lr[grp] * factor : a.lr[grp];
+        const float gr = grad_of(r);
+        adam_elem(pp[j], mm[j], vv[j], gr, lr, a, bc1, bc2);
+        if (OUT == kBwdAdamStore) at(out, r) = gr;
+        if (OUT == kBwdAdamBig) __builtin_nontemporal_store(pp[j], &at(P, r));
+        else at(P, r) = pp[j];
+        __builtin_nontemporal_store(mm[j], &at(M, r));
+        __builtin_nontemporal_store(vv[j], &at(Vv, r));
+      }
+    }
   }
+}
+
+// Several views.  The parameters are read before this thread writes any of them, and a
+// thread touches only its own Gaussian's column.  The SH coefficients and their
+// gradients stay in registers across the views (two waves per SIMD at degree 3; with
+// the coefficients in LDS a third fits only with spills, which cost more than twice the
+// time), and the coefficients serve the fused step as the parameters it updates:
+// 1 000 000 Gaussians in 9 views 361 us, 423 with the rows read again and cached (395
+// if the compiler is not told that two waves are enough: it then orders the loads for
+// more).
+template <int D, BwdOut OUT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_preprocess_bwd(
+    float* P, int n, int stride, const ViewDev* __restrict__ views, int V, const uint32_t* __restrict__ touched,
+    const float* __restrict__ grad2d, float* out, float* M, float* Vv, uint32_t* step, AdamArgs a,
+    const DevStatus* st) {
+#pragma clang fp contract(fast)
+  constexpr bool ADAM = OUT != kBwdStore && OUT != kBwdAccumulate;
+  constexpr int K = (D + 1) * (D + 1);
+  const int g0 = blockIdx.x * 256, g = g0 + threadIdx.x;
+  if (g >= n) return;
+  if (ADAM && st && st->code != GS_OK) return;   // the binning of this step failed: leave the state
+  // the loads of the view loop run ahead of it: the touched flag of view v + 2 and
+  // the 2D gradient of view v + 1 are in flight while view v is processed (at two
+  // waves per SIMD nothing else would cover their latency)
+  uint32_t t_next = V > 0 ? touched[g] : 0u;                  // view v + 1
+  uint32_t t_after = V > 1 ? touched[(size_t)n + g] : 0u;     // view v + 2
+  const uint32_t step_old = ADAM ? step[g] : 0u;
+  GaussF G;
+  gauss_geom_f(P, stride, g, G);
+
+  float gm[3] = {0.f, 0.f, 0.f};       // dL/dmean
+  float gSig[3][3] = {{0.f}};          // symmetric dL/dSigma accumulated over views
+  float go = 0.f;                      // dL/dopacity
+  float gf[3 * K];                     // dL/dSH
+  float f[3 * K];                      // SH coefficients, held across the views
 #pragma unroll
   for (int i = 0; i < 3 * K; ++i) {
-    float* dst = out + (size_t)(11 + i) * stride + g;
-    *dst = accumulate ? *dst + gf[i] : gf[i];
+    gf[i] = 0.f;
+    f[i] = P[(size_t)(11 + i) * stride + g];
   }
+
+  // the per-view learning-rate factor of the fused step (the mean of the scales of
+  // the views that see the Gaussian, else of all), summed in view order as
+  // adam_view_factor does, from the flags the loop reads anyway
+  const bool fold_factor = ADAM && a.n_views == V;
+  float fs = 0.0f, fall = 0.0f;
+  int fc = 0;
+  float g2n[kGrad2D];
+  load_grad2d(grad2d + (size_t)g * kGrad2D, t_next, g2n);
+  for (int v = 0; v < V; ++v) {
+    const uint32_t t_cur = t_next;
+    float g2[kGrad2D];
+#pragma unroll
+    for (int k = 0; k < kGrad2D; ++k) g2[k] = g2n[k];
+    t_next = t_after;
+    if (v + 1 < V) load_grad2d(grad2d + ((size_t)(v + 1) * n + g) * kGrad2D, t_next, g2n);
+    t_after = v + 2 < V ? touched[(size_t)(v + 2) * n + g] : 0u;
+    if (fold_factor) {
+      fall += a.scale[v];
+      if (t_cur != 0u) {
+        fs += a.scale[v];
+        ++fc;
+      }
+    }
+    if (t_cur == 0u) continue;
+    go += g2[5];
+    const float grgb[3] = {g2[6], g2[7], g2[8]};
+    float graw[3], Y[16];
+    colour_grad<D>(views[v], G, f, grgb, graw, Y, gm);
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+      for (int ch = 0; ch < 3; ++ch) gf[3 * k + ch] += graw[ch] * Y[k];
+    geom_grad(views[v], G, g2, gm, gSig);
+  }
+
+  float outv[11];
+  finish_geom(P, stride, g, gSig, gm, go, outv);
+  float factor = 1.0f;
+  if (ADAM) {
+    step[g] = step_old + 1u;
+    factor = fold_factor ? (fc > 0 ? fs / (float)fc : fall / (float)a.n_views) : adam_view_factor(a, touched, n, g);
+  }
+  apply_rows<D, OUT>(P, stride, g0, step_old + 1u, out, M, Vv, a, factor, f,
+                     [&](int r) { return r < 11 ? outv[r < 11 ? r : 0] : gf[r < 11 ? 0 : r - 11]; });
+}
+
+// One view: nothing has to be held across a view loop, so the coefficients' gradients
+// stay the products they are (colour and basis value), and the geometry is done and out
+// of its registers before the coefficients are loaded (143
+// registers at degree 3 and three waves per SIMD, 92 and five without the fused step;
+// holding both coefficients and gradients took 210 and two).  Three backwards of
+// 200 000 Gaussians without the fused step took 135 us with the kernel above, 94 here.
+template <int D, BwdOut OUT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_preprocess_bwd_one(
+    float* P, int n, int stride, const ViewDev* __restrict__ view, const uint32_t* __restrict__ touched,
+    const float* __restrict__ grad2d, float* out, float* M, float* Vv, uint32_t* step, AdamArgs a,
+    const DevStatus* st) {
+#pragma clang fp contract(fast)
+  constexpr bool ADAM = OUT != kBwdStore && OUT != kBwdAccumulate;
+  constexpr int K = (D + 1) * (D + 1);
+  const int g0 = blockIdx.x * 256, g = g0 + threadIdx.x;
+  if (g >= n) return;
+  if (ADAM && st && st->code != GS_OK) return;   // the binning of this step failed: leave the state
+  const uint32_t t_cur = touched[g];
+  const uint32_t step_old = ADAM ? step[g] : 0u;
+  GaussF G;
+  gauss_geom_f(P, stride, g, G);
+  float g2[kGrad2D];
+  load_grad2d(grad2d + (size_t)g * kGrad2D, t_cur, g2);
+  const float grgb[3] = {g2[6], g2[7], g2[8]};
+  float gm[3] = {0.f, 0.f, 0.f};
+  float gSig[3][3] = {{0.f}};
+  if (t_cur != 0u) geom_grad(*view, G, g2, gm, gSig);
+  float outv[11];
+  finish_geom(P, stride, g, gSig, gm, g2[5], outv);
+  // (none of the geometry is held or moved past the coefficients' loads)
+#pragma unroll
+  for (int r = 0; r < 11; ++r) asm volatile("" : "+v"(outv[r])::"memory");
+  float f[3 * K];
+#pragma unroll
+  for (int i = 0; i < 3 * K; ++i) f[i] = (P + (size_t)(11 + i) * stride + g0)[threadIdx.x];
+  float graw[3] = {0.f, 0.f, 0.f}, Y[16] = {0.f};
+  if (t_cur != 0u) {
+    float gmc[3] = {0.f, 0.f, 0.f};
+    colour_grad<D>(*view, G, f, grgb, graw, Y, gmc);
+    for (int k = 0; k < 3; ++k) outv[k] += gmc[k];
+  }
+  float factor = 1.0f;
+  if (ADAM) {
+    step[g] = step_old + 1u;
+    factor = adam_view_factor(a, touched, n, g);
+  }
+  apply_rows<D, OUT>(P, stride, g0, step_old + 1u, out, M, Vv, a, factor, f, [&](int r) {
+#pragma clang fp contract(off)
+    return r < 11 ? outv[r < 11 ? r : 0] : graw[r < 11 ? 0 : (r - 11) % 3] * Y[r < 11 ? 0 : (r - 11) / 3];
+  });
 }
 
 __global__ void k_fill_u32(uint32_t* __restrict__ p, uint32_t value, size_t count) {
@@ -507,12 +616,32 @@ hipError_t launch_preprocess(const float* P, int n, int stride, int D, const Vie
 hipError_t launch_bwd(float* P, int n, int stride, int D, const ViewDev* views, int V, const uint32_t* touched,
                       const float* grad2d, float* grad, int accumulate, int adam, float* M, float* Vv, uint32_t* step,
                       const AdamArgs& a, const DevStatus* st, hipStream_t s) {
-  const int blocks = (n + 255) / 256;
+  const dim3 grid((unsigned)((n + 255) / 256)), block(256);
+  // parameters larger than the 256 MB last-level cache are not there for the next
+  // forward in any case
+  const bool big = (size_t)stride * n_params(D) * 4 > ((size_t)256 << 20);
+  const auto launch = [&](auto degree) {
+    constexpr int DEG = decltype(degree)::value;
+    const auto as = [&](auto mode) {
+      constexpr BwdOut OUT = decltype(mode)::value;
+      if (V == 1)
+        hipLaunchKernelGGL((k_preprocess_bwd_one<DEG, OUT>), grid, block, 0, s, P, n, stride, views, touched, grad2d,
+                           grad, M, Vv, step, a, st);
+      else
+        hipLaunchKernelGGL((k_preprocess_bwd<DEG, OUT>), grid, block, 0, s, P, n, stride, views, V, touched, grad2d,
+                           grad, M, Vv, step, a, st);
+    };
+    if (adam && grad) as(std::integral_constant<BwdOut, kBwdAdamStore>{});
+    else if (adam && big) as(std::integral_constant<BwdOut, kBwdAdamBig>{});
+    else if (adam) as(std::integral_constant<BwdOut, kBwdAdam>{});
+    else if (accumulate) as(std::integral_constant<BwdOut, kBwdAccumulate>{});
+    else as(std::integral_constant<BwdOut, kBwdStore>{});
+  };
   switch (D) {
-    case 0: hipLaunchKernelGGL(k_preprocess_bwd<0>, dim3(blocks), dim3(256), 0, s, P, n, stride, views, V, touched, grad2d, grad, accumulate, adam, M, Vv, step, a, st); break;
-    case 1: hipLaunchKernelGGL(k_preprocess_bwd<1>, dim3(blocks), dim3(256), 0, s, P, n, stride, views, V, touched, grad2d, grad, accumulate, adam, M, Vv, step, a, st); break;
-    case 2: hipLaunchKernelGGL(k_preprocess_bwd<2>, dim3(blocks), dim3(256), 0, s, P, n, stride, views, V, touched, grad2d, grad, accumulate, adam, M, Vv, step, a, st); break;
-    default: hipLaunchKernelGGL(k_preprocess_bwd<3>, dim3(blocks), dim3(256), 0, s, P, n, stride, views, V, touched, grad2d, grad, accumulate, adam, M, Vv, step, a, st); break;
+    case 0: launch(std::integral_constant<int, 0>{}); break;
+    case 1: launch(std::integral_constant<int, 1>{}); break;
+    case 2: launch(std::integral_constant<int, 2>{}); break;
+    default: launch(std::integral_constant<int, 3>{}); break;
   }
   return hipGetLastError();
 }
