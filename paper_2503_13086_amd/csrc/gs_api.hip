@@ -665,12 +665,20 @@ gs_status gs_loss(gs_ctx* c, const float* color, const float* target, float w_l1
   hipStream_t s = (hipStream_t)stream;
   GS_HIP(c, hipSetDevice(c->device));
   gs_status st;
-  if ((st = ensure(c, c->lossp, (size_t)loss_tiles(c->hviews.data(), c->V) * 16, s)) != GS_OK) return st;
-  if (w_dssim != 0.0f && (st = ensure(c, c->aux, (size_t)c->P * 9 * 4, s)) != GS_OK) return st;
+  if ((st = ensure(c, c->lossp, (size_t)loss_partials(c->hviews.data(), c->V) * 16, s)) != GS_OK) return st;
+  // a gradient written over one of the images goes through a buffer: the SSIM term
+  // reads both around every pixel
+  const size_t image = (size_t)c->P * 3 * 4;
+  const auto over = [&](const float* im) {
+    const uintptr_t d = (uintptr_t)dL_dcolor, i = (uintptr_t)im;
+    return d < i + image && i < d + image;
+  };
+  const bool via = w_dssim != 0.0f && (over(color) || over(target));
+  if (via && (st = ensure(c, c->aux, image, s)) != GS_OK) return st;
   Prof pr(c, GS_K_LOSS, s);
   GS_HIP(c, launch_loss_dev(c->views.as<ViewDev>(), c->hviews.data(), c->V, color, target, w_l1, w_dssim,
-                            c->lossp.as<double>(), w_dssim != 0.0f ? c->aux.as<float>() : nullptr, loss_out,
-                            dL_dcolor, s));
+                            c->lossp.as<double>(), loss_out, via ? c->aux.as<float>() : dL_dcolor, s));
+  if (via) GS_HIP(c, hipMemcpyAsync(dL_dcolor, c->aux.as<float>(), image, hipMemcpyDeviceToDevice, s));
   return GS_OK;
 }
 
@@ -693,10 +701,9 @@ gs_status gs_loss_noalloc(gs_ctx* c, const float* color, const float* target, fl
   void* sp = scratch_for(c->device);
   if (!sp) return fail(c, GS_ERR_UNSUPPORTED, "gs_loss_noalloc: no scratch address for this device");
   GS_HIP(c, hipSetDevice(c->device));
-  // every tile's sums are written before they are read: nothing to clear; the SSIM
-  // term runs as the fused kernel, which keeps its per-pixel terms in LDS
+  // every tile's sums are written before they are read: nothing to clear
   GS_HIP(c, launch_loss_dev(c->views.as<ViewDev>(), c->hviews.data(), c->V, color, target, w_l1, w_dssim,
-                            reinterpret_cast<double*>(sp), nullptr, loss_out, dL_dcolor, (hipStream_t)stream));
+                            reinterpret_cast<double*>(sp), loss_out, dL_dcolor, (hipStream_t)stream));
   return GS_OK;
 }
 

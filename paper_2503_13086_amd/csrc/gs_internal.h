@@ -346,18 +346,20 @@ hipError_t launch_ordered_sum(const uint32_t* pair_rec, size_t K_cap, const unsi
                               uint32_t* keys_b, uint32_t* vals_b, uint2* eranges, SortScratch scratch,
                               float* grad2d, hipStream_t s);
 
-// Loss over all views in 32x32-pixel tiles: loss_tiles() tiles, partials 2 doubles
-// per tile; aux 9 floats per pixel for the SSIM term, or NULL for the fused SSIM
-// kernel, which needs none.
+// Loss over all views.  partials: 2 doubles for each of loss_partials() tiles, which are
+// at most loss_tiles() (the views' 32x32 tiles) where those are more than 8192.
+// dL_dcolor must not overlap the images when w_dssim != 0 (neighbouring tiles read
+// them after this one's gradient is written).
 int loss_tiles(const ViewDev* hviews, int V);
+int loss_partials(const ViewDev* hviews, int V);
 // Eq. 9 on the soft count asum [P]: per-view loss w std (loss_out, may be NULL)
 // and dL/dG [P]; partials: V x load_chunks doubles2, stats: V doubles2
 int load_chunks(const ViewDev* hviews, int V);
 hipError_t launch_load_balance(const ViewDev* dviews, const ViewDev* hviews, int V, const float* asum, float w,
                                double* partials, double* stats, double* loss_out, float* dG, hipStream_t s);
 hipError_t launch_loss_dev(const ViewDev* dviews, const ViewDev* hviews, int V, const float* color,
-                           const float* target, float w_l1, float w_dssim, double* partials, float* aux,
-                           double* loss_out, float* dL_dcolor, hipStream_t s);
+                           const float* target, float w_l1, float w_dssim, double* partials, double* loss_out,
+                           float* dL_dcolor, hipStream_t s);
 
 struct AdamArgs {
   float lr[GS_N_GROUPS];

@@ -2,10 +2,7 @@
 //
 // Per view: w_l1 * mean|x - y| + w_dssim * (1 - mean SSIM(x, y)), SSIM per channel
 // from windowed means under a normalised 11x11 Gaussian window (sigma 1.5, zero
-// padding), C1 = 0.01^2, C2 = 0.03^2.  All views share one launch of 32x32-pixel
-// output tiles (256 threads); the separable window runs in two register-blocked
-// passes per map (a thread filters a run of consecutive columns of a row, then a
-// run of rows of a column), one map at a time through LDS.  E[x^2] and E[y^2]
+// padding), C1 = 0.01^2, C2 = 0.03^2.  All views share one launch.  E[x^2] and E[y^2]
 // enter SSIM only through their sum (in D2), so four maps are filtered: x, y,
 // x^2 + y^2 and xy.
 //
@@ -14,22 +11,10 @@
 // respect to the windowed statistics (mx, E[x^2], E[xy]) are
 //   A = 2 my (N2 - N1) / (D1 D2) + 2 mx S (1/D2 - 1/D1),  B = -S / D2,
 //   Cc = 2 N1 / (D1 D2),
-// and dS_mean/dx = (window * A + 2 x (window * B) + y (window * Cc)) / N, with 1/D1
-// and 1/D2 taken once per pixel from the hardware reciprocal.
-//
-// Two forms of the SSIM term:
-// * gs_loss: k_ssim_fwd forms the statistics over each tile (a 42x42 halo staged)
-//   and stores A, B, Cc (36 B per pixel); k_ssim_bwd filters them the same way (the
-//   window is symmetric) and adds the L1 term.
-// * gs_loss_noalloc: k_ssim_fused does both per tile with nothing but the images,
-//   the gradient and the per-tile sums in HBM: it stages the 52x52 patch that
-//   reaches the tile through two windows, forms the statistics over the 42x42
-//   region whose SSIM terms reach the tile, turns them into A, B, Cc there in the
-//   LDS the patch occupied, and filters those over the tile.  About a third of the
-//   HBM traffic, 1.4x the filtering work (the 42x42 region is recomputed by
-//   neighbouring tiles); the kernel is bound by instruction issue, so on this chip
-//   it is the slower of the two (0.57 against 0.45 ms at 10 Mpix).
-// Loss sums are reduced per tile in FP64.
+// and dS_mean/dx = (window * A + 2 x (window * B) + y (window * Cc)) / N (the window
+// is symmetric), with 1/D1 and 1/D2 taken once per pixel from the hardware reciprocal.
+// k_ssim forms all of it in one pass over the images.
+// Loss sums are reduced per workgroup in FP64.
 //
 // The load-balancing term of Eq. 9 (kernels at the end) works on the soft
 // per-pixel Gaussian count the forward writes.
@@ -38,16 +23,11 @@
 namespace gsk {
 namespace {
 
-constexpr int LT = 32;              // output tile edge
+constexpr int LT = 32;              // k_l1's tile edge
 constexpr int R = 5;                // window radius
 constexpr int TAPS = 2 * R + 1;
-constexpr int HALO = LT + 2 * R;    // 42
-constexpr int HS = HALO;            // LDS row stride (unpadded: the backward then fits six workgroups per CU)
-constexpr int HSEG = 8;             // horizontal outputs per thread
-constexpr int VSEG = 4;             // vertical outputs per thread
-constexpr int IN = LT + 4 * R;      // 52: the fused kernel's patch (two windows around the tile)
-constexpr int FVSEG = 7;            // vertical outputs per thread of its 42-high forward maps
-constexpr int FTASKS = HALO * (HALO / FVSEG);   // 252 threads hold its forward statistics
+constexpr int kSsimOccupancy = 3;   // k_ssim's wavefronts per SIMD (147 registers; at four they spill)
+constexpr int SW = 64 - 4 * R;      // k_ssim: output columns of a wavefront (two windows less than its lanes)
 constexpr float kC1 = 0.01f * 0.01f;
 constexpr float kC2 = 0.03f * 0.03f;
 
@@ -55,7 +35,8 @@ struct Win {
   float w[TAPS];
 };
 
-// global 32-tile offset of each view (n_views + 1 entries)
+// global offset of each view's tiles (n_views + 1 entries): 32x32 pixels (k_l1) or SW
+// columns by a number of rows (k_ssim)
 struct LossTiles {
   int32_t off[GS_MAX_VIEWS + 1];
 };
@@ -85,25 +66,13 @@ __host__ __device__ inline int xcd_tile_chunk(int n_tiles) { return (n_tiles + k
 
 __device__ inline int xcd_tile(int b, int n_tiles) { return (b % kXcds) * xcd_tile_chunk(n_tiles) + b / kXcds; }
 
-__device__ inline TileLoc loss_tile(const ViewDev* __restrict__ views, const LossTiles& lt, int V, int tile) {
+__device__ inline TileLoc loss_tile(const ViewDev* __restrict__ views, const LossTiles& lt, int V, int tile, int tw,
+                                    int th) {
   int v = 0;
   while (v + 1 < V && tile >= lt.off[v + 1]) ++v;
-  const int nx = (views[v].W + LT - 1) / LT;
+  const int nx = (views[v].W + tw - 1) / tw;
   const int local = tile - lt.off[v];
-  return TileLoc{v, (local % nx) * LT, (local / nx) * LT};
-}
-
-// Stage a HALO x HALO patch of q planes (zero outside the image) into LDS.
-template <int Q>
-__device__ inline void stage_halo(float (*dst)[HALO * HS], const float* const* src, int W, int H, int x0, int y0) {
-  for (int i = threadIdx.x; i < HALO * HALO; i += blockDim.x) {
-    const int r = i / HALO, c = i % HALO;
-    const int gx = x0 - R + c, gy = y0 - R + r;
-    const bool in = gx >= 0 && gx < W && gy >= 0 && gy < H;
-    const size_t p = (size_t)gy * W + gx;
-#pragma unroll
-    for (int q = 0; q < Q; ++q) dst[q][r * HS + c] = in ? src[q][p] : 0.0f;
-  }
+  return TileLoc{v, (local % nx) * tw, (local / nx) * th};
 }
 
 __global__ __launch_bounds__(256) void k_l1(const ViewDev* __restrict__ views, int V, LossTiles lt,
@@ -112,7 +81,7 @@ __global__ __launch_bounds__(256) void k_l1(const ViewDev* __restrict__ views, i
   __shared__ double sh[4];
   const int tile = xcd_tile(blockIdx.x, lt.off[V]);
   if (tile >= lt.off[V]) return;
-  const TileLoc t = loss_tile(views, lt, V, tile);
+  const TileLoc t = loss_tile(views, lt, V, tile, LT, LT);
   const ViewDev& cv = views[t.v];
   const size_t hw = (size_t)cv.W * cv.H;
   const size_t base = 3 * (size_t)cv.pix_off;
@@ -132,391 +101,245 @@ __global__ __launch_bounds__(256) void k_l1(const ViewDev* __restrict__ views, i
   if (threadIdx.x == 0) partials[tile] = make_double2(tot, 0.0);
 }
 
-// Horizontal pass: out[q][r][c] (r < HALO, c < LT) = sum_k w[k] f_q(r, c + k) where the
-// Q outputs are formed from the NIN staged inputs by `form`.
-template <int NIN, int Q, class F>
-__device__ inline void hpass(const float (*in)[HALO * HS], float (*out)[HALO * LT], const Win& win, F form) {
-  const int task = threadIdx.x;
-  if (task < HALO * (LT / HSEG)) {
-    const int r = task / (LT / HSEG), c0 = (task % (LT / HSEG)) * HSEG;
-    float acc[Q][HSEG];
-#pragma unroll
-    for (int q = 0; q < Q; ++q)
-#pragma unroll
-      for (int j = 0; j < HSEG; ++j) acc[q][j] = 0.0f;
-#pragma unroll
-    for (int k = 0; k < HSEG + 2 * R; ++k) {
-      float v[NIN];
-#pragma unroll
-      for (int i = 0; i < NIN; ++i) v[i] = in[i][r * HS + c0 + k];
-      float f[Q];
-      form(v, f);
-#pragma unroll
-      for (int j = 0; j < HSEG; ++j) {
-        const int tap = k - j;
-        if (tap >= 0 && tap < TAPS) {
-#pragma unroll
-          for (int q = 0; q < Q; ++q) acc[q][j] = __fmaf_rn(win.w[tap], f[q], acc[q][j]);
-        }
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < Q; ++q)
-#pragma unroll
-      for (int j = 0; j < HSEG; ++j) out[q][r * LT + c0 + j] = acc[q][j];
-  }
-}
-
-// Vertical pass for this thread's 4 output rows of one column.
+// Q vertical windows: acc[q][s] sums output row s mod TAPS, which the TAPS input rows
+// from it on reach.  Takes input row u mod TAPS (u a constant, so that the sums rotate
+// through the registers without moves) and returns the row that is then complete.
 template <int Q>
-__device__ inline void vpass(const float (*in)[HALO * LT], const Win& win, int col, int r0, float (&res)[Q][VSEG]) {
+__device__ inline void window_rows(int u, const float (&w)[R + 1], const float (&v)[Q], float (&acc)[Q][TAPS],
+                                   float (&fin)[Q]) {
 #pragma unroll
-  for (int q = 0; q < Q; ++q)
+  for (int k = 0; k < TAPS; ++k) {
+    const int s = (u - k + TAPS) % TAPS;
 #pragma unroll
-    for (int j = 0; j < VSEG; ++j) res[q][j] = 0.0f;
-#pragma unroll
-  for (int k = 0; k < VSEG + 2 * R; ++k) {
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const float f = in[q][(r0 + k) * LT + col];
-#pragma unroll
-      for (int j = 0; j < VSEG; ++j) {
-        const int tap = k - j;
-        if (tap >= 0 && tap < TAPS) res[q][j] = __fmaf_rn(win.w[tap], f, res[q][j]);
-      }
-    }
+    for (int q = 0; q < Q; ++q)
+      acc[q][s] = k == 0 ? w[0] * v[q] : __fmaf_rn(w[k < R ? k : TAPS - 1 - k], v[q], acc[q][s]);
   }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) fin[q] = acc[q][(u + 1) % TAPS];
 }
 
-// One windowed map of the staged planes (form makes its value from theirs) for
-// this thread's VSEG outputs; the workgroup's LDS map buffer is free again on return.
-template <int NIN, class F>
-__device__ inline void window_map(const float (*in)[HALO * HS], float (*hb)[HALO * LT], const Win& win, int col,
-                                  int r0, F form, float (&res)[VSEG]) {
-  hpass<NIN, 1>(in, hb, win, form);
-  __syncthreads();
-  float mq[1][VSEG];
-  vpass<1>(hb, win, col, r0, mq);
-  // the sums are formed here: left alone, the compiler sinks them into the
-  // per-pixel branches at the end and keeps every loaded tap live until then
-#pragma unroll
-  for (int j = 0; j < VSEG; ++j) {
-    res[j] = mq[0][j];
-    asm volatile("" : "+v"(res[j]));
-  }
-  __syncthreads();
+// Orders a wavefront's LDS accesses (which execute in order) for the compiler: lanes
+// read what other lanes wrote.
+__device__ inline void lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Register budgets: 8 waves per SIMD for the forward (59 VGPRs; left alone the
-// compiler takes 68 and runs 7), 6 for the backward (its LDS allows 6 workgroups).
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_ssim_fwd(const ViewDev* __restrict__ views, int V, LossTiles lt,
-                                                   const float* __restrict__ x, const float* __restrict__ y,
-                                                   float* __restrict__ aux, Win win, double2* __restrict__ partials) {
-  __shared__ float sin_[2][HALO * HS];
-  __shared__ float hbuf[1][HALO * LT];   // the four maps one after another: 20 KB of LDS
-  __shared__ double sh[4];
-  const int tile = xcd_tile(blockIdx.x, lt.off[V]);
+// The horizontal window: lane l's sums over lanes l .. l + TAPS - 1 of Q values, through
+// one 16-byte LDS word per lane (the last TAPS - 1 lanes read past the 64 values that
+// are there and have no result).  In two parts, for other work while the words travel.
+template <int Q>
+struct Neighbours {
+  float v[TAPS][Q];
+};
+template <int Q>
+__device__ inline void window_cols_load(float4* buf, const float (&v)[Q], Neighbours<Q>& nb) {
+  static_assert(Q == 3 || Q == 4, "one 16-byte word");
+  const int lane = __lane_id();
+  lds_order();   // the reads of the row before
+  buf[lane] = make_float4(v[0], v[1], v[2], Q > 3 ? v[Q - 1] : 0.0f);
+  lds_order();
+#pragma unroll
+  for (int q = 0; q < Q; ++q) nb.v[0][q] = v[q];
+#pragma unroll
+  for (int k = 1; k < TAPS; ++k) {
+    const float4 n = buf[lane + k];
+    const float nv[4] = {n.x, n.y, n.z, n.w};
+#pragma unroll
+    for (int q = 0; q < Q; ++q) nb.v[k][q] = nv[q];
+  }
+}
+template <int Q>
+__device__ inline void window_cols_sum(const float (&w)[R + 1], const Neighbours<Q>& nb, float (&out)[Q]) {
+#pragma unroll
+  for (int k = 0; k < TAPS; ++k)
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      out[q] = k == 0 ? w[0] * nb.v[k][q] : __fmaf_rn(w[k < R ? k : TAPS - 1 - k], nb.v[k][q], out[q]);
+  // the sums are formed here: left alone, the compiler moves them to where the vertical
+  // windows are used and keeps every word live until then
+#pragma unroll
+  for (int q = 0; q < Q; ++q) asm volatile("" : "+v"(out[q]));
+}
+
+// The SSIM term and both terms' gradient.  A wavefront takes one channel of SW columns
+// by `rows` rows and walks down them, a lane per column: each row's four maps go through
+// LDS into the horizontal windows and from there into the vertical ones; the row these
+// finish gives S and A, B, Cc, which go through the second horizontal and vertical
+// windows, and the row those finish is a row of the gradient.  So each image is read once (and a fifth around it), nothing else but
+// the gradient touches HBM and no barrier is met.  What it does again: a tile passes
+// over rows + 4R rows and 64 columns for its SW.
+// Bound by instruction issue (about 185 vector instructions a row, of which 154 the
+// windows' multiply-adds) and the 22 16-byte LDS accesses a row beside it.  It replaced
+// two kernels over 32x32 tiles with the statistics in HBM between them (36 bytes a pixel
+// written and read) and, for gs_loss_noalloc, one over 52x52 patches: 10.1 Mpix in 9
+// views 431 -> 290 us (both terms and the final sums), 1600x1067 91 -> 76, 1296x864
+// 71 -> 56, three views of 0.2 Mpix in all 45 -> 27.
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kSsimOccupancy))) void k_ssim(
+    const ViewDev* __restrict__ views, int V, LossTiles lt, int rows, const float* __restrict__ x,
+    const float* __restrict__ y, Win win, float w_l1, float w_dssim, float* __restrict__ grad,
+    double2* __restrict__ partials) {
+  static_assert(WAVES == 1 || WAVES == 3, "a channel or all three");
+  __shared__ float4 bufs[WAVES][2][64 + TAPS - 1];
+  __shared__ double2 sums[3];
+  const int part = xcd_tile(blockIdx.x, WAVES == 1 ? 3 * lt.off[V] : lt.off[V]);
+  const int tile = WAVES == 1 ? part / 3 : part;
   if (tile >= lt.off[V]) return;
-  const TileLoc t = loss_tile(views, lt, V, tile);
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64), ch = WAVES == 1 ? part % 3 : wave;
+  float4 (*buf)[64 + TAPS - 1] = bufs[wave];
+  const TileLoc t = loss_tile(views, lt, V, tile, SW, rows);
   const ViewDev& cv = views[t.v];
-  const size_t hw = (size_t)cv.W * cv.H;
-  const size_t base = 3 * (size_t)cv.pix_off;
-  const int col = threadIdx.x % LT, r0 = (threadIdx.x / LT) * VSEG;
-  double sl1 = 0.0, sss = 0.0;
-  for (int ch = 0; ch < 3; ++ch) {
-    const float* src[2] = {x + base + ch * hw, y + base + ch * hw};
-    stage_halo<2>(sin_, src, cv.W, cv.H, t.x0, t.y0);
-    __syncthreads();
-    float m[4][VSEG];
-    window_map<2>(sin_, hbuf, win, col, r0, [](const float* v, float* f) { f[0] = v[0]; }, m[0]);
-    window_map<2>(sin_, hbuf, win, col, r0, [](const float* v, float* f) { f[0] = v[1]; }, m[1]);
-    window_map<2>(sin_, hbuf, win, col, r0,
-                  [](const float* v, float* f) { f[0] = __fmaf_rn(v[0], v[0], v[1] * v[1]); }, m[2]);
-    window_map<2>(sin_, hbuf, win, col, r0, [](const float* v, float* f) { f[0] = v[0] * v[1]; }, m[3]);
-    float* ac = aux + (size_t)cv.pix_off * 9 + (size_t)ch * 3 * hw;
-#pragma unroll
-    for (int j = 0; j < VSEG; ++j) {
-      const int px = t.x0 + col, py = t.y0 + r0 + j;
-      if (px < cv.W && py < cv.H) {
-        const float mx = m[0][j], my = m[1][j];
-        const float sxy = m[3][j] - mx * my;
-        const float N1 = 2.0f * mx * my + kC1, N2 = 2.0f * sxy + kC2;
-        const float M2 = mx * mx + my * my;
-        const float D1 = M2 + kC1, D2 = (m[2][j] - M2) + kC2;
-        // hardware reciprocals (1 ulp): D1, D2 >= C1 > 0
-        const float r1 = __builtin_amdgcn_rcpf(D1), r2 = __builtin_amdgcn_rcpf(D2);
-        const float rden = r1 * r2;
-        const float S = (N1 * N2) * rden;
-        const size_t p = (size_t)py * cv.W + px;
-        ac[p] = 2.0f * my * (N2 - N1) * rden + 2.0f * mx * S * (r2 - r1);
-        ac[p + hw] = -S * r2;
-        ac[p + 2 * hw] = 2.0f * N1 * rden;
-        const float xv = sin_[0][(r0 + j + R) * HS + col + R];
-        const float yv = sin_[1][(r0 + j + R) * HS + col + R];
-        sl1 += fabs((double)(xv - yv));
-        sss += (double)S;
-      }
-    }
-    __syncthreads();
-  }
-  const double t1 = block_sum_d(sl1, sh);
-  const double t2 = block_sum_d(sss, sh);
-  if (threadIdx.x == 0) partials[tile] = make_double2(t1, t2);
-}
-
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k_ssim_bwd(const ViewDev* __restrict__ views, int V, LossTiles lt,
-                                                   const float* __restrict__ x, const float* __restrict__ y,
-                                                   const float* __restrict__ aux, Win win, float w_l1, float w_dssim,
-                                                   float* __restrict__ grad) {
-  __shared__ float sin_[3][HALO * HS];
-  __shared__ float hbuf[1][HALO * LT];   // the three maps filtered one after another: 26 KB of LDS
-  const int tile = xcd_tile(blockIdx.x, lt.off[V]);
-  if (tile >= lt.off[V]) return;
-  const TileLoc t = loss_tile(views, lt, V, tile);
-  const ViewDev& cv = views[t.v];
-  const size_t hw = (size_t)cv.W * cv.H;
-  const size_t base = 3 * (size_t)cv.pix_off;
+  const int W = cv.W, H = cv.H, lane = __lane_id();
+  const size_t hw = (size_t)W * H;
+  const size_t plane = 3 * (size_t)cv.pix_off + ch * hw;
   const float invN = 1.0f / (float)(3 * hw);
-  const int col = threadIdx.x % LT, r0 = (threadIdx.x / LT) * VSEG;
-  for (int ch = 0; ch < 3; ++ch) {
-    const float* ac = aux + (size_t)cv.pix_off * 9 + (size_t)ch * 3 * hw;
-    const float* src[3] = {ac, ac + hw, ac + 2 * hw};
-    stage_halo<3>(sin_, src, cv.W, cv.H, t.x0, t.y0);
-    // this thread's image values, fetched now so the loads overlap the filtering
-    float xs[VSEG], ys[VSEG];
+  float w[R + 1];   // (in vector registers: a scalar operand halves the rate of an FMA)
 #pragma unroll
-    for (int j = 0; j < VSEG; ++j) {
-      const int px = t.x0 + col, py = t.y0 + r0 + j;
-      const bool in = px < cv.W && py < cv.H;
-      const size_t p = base + ch * hw + (size_t)py * cv.W + px;
-      xs[j] = in ? x[p] : 0.0f;
-      ys[j] = in ? y[p] : 0.0f;
-    }
-    __syncthreads();
-    float m[3][VSEG];
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-      window_map<1>(sin_ + q, hbuf, win, col, r0, [](const float* v, float* f) { f[0] = v[0]; }, m[q]);
-#pragma unroll
-    for (int j = 0; j < VSEG; ++j) {
-      const int px = t.x0 + col, py = t.y0 + r0 + j;
-      if (px < cv.W && py < cv.H) {
-        const size_t p = base + ch * hw + (size_t)py * cv.W + px;
-        const float xv = xs[j], yv = ys[j];
-        const float d = xv - yv;
-        const float l1 = w_l1 * invN * (float)((d > 0.0f) - (d < 0.0f));
-        grad[p] = l1 - w_dssim * invN * (m[0][j] + 2.0f * xv * m[1][j] + yv * m[2][j]);
-      }
-    }
-    __syncthreads();
+  for (int k = 0; k <= R; ++k) {
+    w[k] = win.w[k];
+    asm volatile("" : "+v"(w[k]));
   }
-}
-
-// ---- fused SSIM (gs_loss_noalloc) ----
-
-// Horizontal pass over ROWS rows of one or two staged planes (row stride IS) into
-// an OW-wide map (row stride OW): out(r, c) = sum_k w[k] form(in0, in1)(r, c + k).
-// A thread filters SEG consecutive columns of one row; a row's tasks start at
-// min(s SEG, OW - SEG), so the last may repeat columns of the one before it, with
-// bit-identical values (same operations in the same order).
-template <int ROWS, int IS, int OW, int SEG, class F>
-__device__ inline void row_pass(const float* in0, const float* in1, float* out, const Win& win, F form) {
-  constexpr int NSEG = (OW + SEG - 1) / SEG;
-  static_assert(ROWS * NSEG <= 256, "one task per thread");
-  const int task = threadIdx.x;
-  if (task < ROWS * NSEG) {
-    const int r = task / NSEG, s = task % NSEG;
-    const int c0 = min(s * SEG, OW - SEG);
-    float acc[SEG];
+  // Lane l reads column x0 - 2R + l, has the statistics of column x0 - R + l (l < 54) and
+  // the gradient of column x0 + l (l < SW).
+  const int cin = t.x0 - 2 * R + lane, cst = cin + R, cout = t.x0 + lane;
+  const bool st_ok = cst >= 0 && cst < W, out_ok = lane < SW && cout < W;
+  const bool st_own = st_ok && lane >= R && lane < SW + R;   // counted here
+  const int y_end = min(t.y0 + rows, H);                     // rows of this tile: [y0, y_end)
+  const int n_in = y_end - t.y0 + 4 * R;                     // input rows y0 - 2R ..
+  // The images go through buffer descriptors that begin at the first row read (or the
+  // tile's own first row) and end with the image: what lies outside reads as zero, the
+  // padding, and is not written, with no branch around a load or a store (at which all
+  // loads in flight would be waited for).  Columns outside get an offset that no row
+  // brings back in range.
+  const uint32_t pitch = 4u * (uint32_t)W, off_image = 0x80000000u;
+  const int r_in = max(t.y0 - 2 * R, 0);
+  const auto rows_of = [&](const float* im, int r) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(im) + plane + (size_t)r * W, 0,
+                                             (int)(pitch * (uint32_t)min(H - r, rows + 4 * R)), 0x00020000);
+  };
+  const __amdgpu_buffer_rsrc_t xi = rows_of(x, r_in), yi = rows_of(y, r_in), xo = rows_of(x, t.y0),
+                               yo = rows_of(y, t.y0), go = rows_of(grad, t.y0);
+  const auto at = [](__amdgpu_buffer_rsrc_t im, uint32_t off) {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(im, off, 0, 0));
+  };
+  // offsets of the next row to load, of the next row whose values are loaded for the
+  // gradient, and of the next gradient row to store (the last two begin above the tile)
+  uint32_t off_in = (cin >= 0 && cin < W ? 4u * (uint32_t)cin : off_image) +
+                    pitch * (uint32_t)(t.y0 - 2 * R - r_in);
+  uint32_t off_out = (out_ok ? 4u * (uint32_t)cout : off_image) - pitch * (uint32_t)(2 * R + 1);
+  float acc1[4][TAPS], acc2[3][TAPS];
 #pragma unroll
-    for (int j = 0; j < SEG; ++j) acc[j] = 0.0f;
+  for (int j = 0; j < TAPS; ++j) {
 #pragma unroll
-    for (int k = 0; k < SEG + 2 * R; ++k) {
-      const int q = r * IS + c0 + k;
-      const float f = form(in0[q], in1 ? in1[q] : 0.0f);
+    for (int q = 0; q < 4; ++q) acc1[q][j] = 0.0f;
 #pragma unroll
-      for (int j = 0; j < SEG; ++j) {
-        const int tap = k - j;
-        if (tap >= 0 && tap < TAPS) acc[j] = __fmaf_rn(win.w[tap], f, acc[j]);
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < SEG; ++j) out[r * OW + c0 + j] = acc[j];
+    for (int q = 0; q < 3; ++q) acc2[q][j] = 0.0f;
   }
-}
-
-// Vertical pass of an OW-wide half-filtered map for SEG consecutive rows of one
-// column (rows r0 .. r0 + SEG - 1 of the result; input rows r0 .. r0 + SEG + 9).
-template <int OW, int SEG>
-__device__ inline void col_pass(const float* hb, const Win& win, int col, int r0, bool active, float (&res)[SEG]) {
-#pragma unroll
-  for (int j = 0; j < SEG; ++j) res[j] = 0.0f;
-  if (!active) return;
-#pragma unroll
-  for (int k = 0; k < SEG + 2 * R; ++k) {
-    const float f = hb[(r0 + k) * OW + col];
-#pragma unroll
-    for (int j = 0; j < SEG; ++j) {
-      const int tap = k - j;
-      if (tap >= 0 && tap < TAPS) res[j] = __fmaf_rn(win.w[tap], f, res[j]);
-    }
-  }
-}
-
-// The sums are formed where they are pinned (see window_map).
-template <int N>
-__device__ inline void pin(float (&res)[N]) {
-#pragma unroll
-  for (int j = 0; j < N; ++j) asm volatile("" : "+v"(res[j]));
-}
-
-// Forward statistics: maps of the 52x52 patch over the 42x42 region (rows in runs
-// of FHSEG = 11: 208 row tasks; columns in runs of FVSEG = 7: 252 threads).
-// Backward: maps of the 42x42 A, B, Cc planes over the 32x32 tile (runs of 6: 252
-// row tasks; runs of VSEG = 4 rows: all 256 threads).
-constexpr int FHRUN = 11;
-constexpr int BHRUN = 6;
-
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_ssim_fused(const ViewDev* __restrict__ views, int V, LossTiles lt,
-                                               const float* __restrict__ x, const float* __restrict__ y, Win win,
-                                               float w_l1, float w_dssim, float* __restrict__ grad,
-                                               double2* __restrict__ partials) {
-  // the staged patch (two 52x52 planes), later the A, B, Cc planes of the 42x42
-  // region; two half-filtered maps (one is filled while the other is read, one
-  // barrier per map): 39 KB of LDS, four workgroups per CU
-  __shared__ float sp[2 * IN * IN];
-  __shared__ float hb[2][IN * HALO];
-  __shared__ double sh[4];
-  static_assert(3 * HALO * HS <= 2 * IN * IN, "A, B, Cc planes fit where the patch was");
-  static_assert(HALO * LT <= IN * HALO, "backward half-filtered maps fit");
-  const int tile = xcd_tile(blockIdx.x, lt.off[V]);
-  if (tile >= lt.off[V]) return;
-  const TileLoc t = loss_tile(views, lt, V, tile);
-  const ViewDev& cv = views[t.v];
-  const size_t hw = (size_t)cv.W * cv.H;
-  const size_t base = 3 * (size_t)cv.pix_off;
-  const float invN = 1.0f / (float)(3 * hw);
-  // forward statistics: region column fc, rows fr0 .. fr0 + 6 (threads < 252);
-  // gradient: tile column col, rows r0 .. r0 + 3
-  const int fc = threadIdx.x % HALO, fr0 = (threadIdx.x / HALO) * FVSEG;
-  const bool factive = (int)threadIdx.x < FTASKS;
-  const int col = threadIdx.x % LT, r0 = (threadIdx.x / LT) * VSEG;
-  const float* X = sp;
-  const float* Y = sp + IN * IN;
   double sl1 = 0.0, sss = 0.0;
-  for (int ch = 0; ch < 3; ++ch) {
-    const float* xc = x + base + ch * hw;
-    const float* yc = y + base + ch * hw;
-    for (int i = threadIdx.x; i < IN * IN; i += blockDim.x) {
-      const int r = i / IN, c = i % IN;
-      const int gx = t.x0 - 2 * R + c, gy = t.y0 - 2 * R + r;
-      const bool in = gx >= 0 && gx < cv.W && gy >= 0 && gy < cv.H;
-      const size_t p = (size_t)gy * cv.W + gx;
-      sp[i] = in ? xc[p] : 0.0f;
-      sp[IN * IN + i] = in ? yc[p] : 0.0f;
-    }
-    __syncthreads();
-    float xs[VSEG], ys[VSEG];
+  // image values of the next AHEAD rows
+  constexpr int AHEAD = 2;
+  float nx[AHEAD], ny[AHEAD];
 #pragma unroll
-    for (int j = 0; j < VSEG; ++j) {
-      xs[j] = X[(r0 + j + 2 * R) * IN + col + 2 * R];
-      ys[j] = Y[(r0 + j + 2 * R) * IN + col + 2 * R];
-    }
-    // windowed x, y, x^2 + y^2 (E[x^2] and E[y^2] enter S only through their sum,
-    // in D2) and xy; map q's vertical pass runs beside map q + 1's horizontal one
-    const auto fx = [](float a, float b) { return a; };
-    const auto fy = [](float a, float b) { return b; };
-    const auto fss = [](float a, float b) { return __fmaf_rn(a, a, b * b); };
-    const auto fxy = [](float a, float b) { return a * b; };
-    float m[4][FVSEG];
-    row_pass<IN, IN, HALO, FHRUN>(X, Y, hb[0], win, fx);
-    __syncthreads();
-    col_pass<HALO, FVSEG>(hb[0], win, fc, fr0, factive, m[0]);
-    pin(m[0]);
-    row_pass<IN, IN, HALO, FHRUN>(X, Y, hb[1], win, fy);
-    __syncthreads();
-    col_pass<HALO, FVSEG>(hb[1], win, fc, fr0, factive, m[1]);
-    pin(m[1]);
-    row_pass<IN, IN, HALO, FHRUN>(X, Y, hb[0], win, fss);
-    __syncthreads();
-    col_pass<HALO, FVSEG>(hb[0], win, fc, fr0, factive, m[2]);
-    pin(m[2]);
-    row_pass<IN, IN, HALO, FHRUN>(X, Y, hb[1], win, fxy);
-    __syncthreads();
-    col_pass<HALO, FVSEG>(hb[1], win, fc, fr0, factive, m[3]);
-    pin(m[3]);
-    // every thread is past its last read of the patch (the barrier before the last
-    // vertical pass): A, B, Cc go where it was
-    float* pa = sp;
-    if (factive) {
-#pragma unroll
-      for (int j = 0; j < FVSEG; ++j) {
-        const int gx = t.x0 - R + fc, gy = t.y0 - R + fr0 + j;
-        float A = 0.0f, B = 0.0f, Cc = 0.0f;
-        if (gx >= 0 && gx < cv.W && gy >= 0 && gy < cv.H) {
-          const float mx = m[0][j], my = m[1][j];
-          const float sxy = m[3][j] - mx * my;
-          const float N1 = 2.0f * mx * my + kC1, N2 = 2.0f * sxy + kC2;
-          const float M2 = mx * mx + my * my;
-          const float D1 = M2 + kC1, D2 = (m[2][j] - M2) + kC2;
-          // hardware reciprocals (1 ulp): D1, D2 >= C1 > 0
-          const float r1 = __builtin_amdgcn_rcpf(D1), r2 = __builtin_amdgcn_rcpf(D2);
-          const float rden = r1 * r2;
-          const float S = (N1 * N2) * rden;
-          A = 2.0f * my * (N2 - N1) * rden + 2.0f * mx * S * (r2 - r1);
-          B = -S * r2;
-          Cc = 2.0f * N1 * rden;
-          const int lx = fc - R, ly = fr0 + j - R;   // inside the tile: its SSIM term is counted here
-          if (lx >= 0 && lx < LT && ly >= 0 && ly < LT) sss += (double)S;
-        }
-        const int q = (fr0 + j) * HS + fc;
-        pa[q] = A;
-        pa[HALO * HS + q] = B;
-        pa[2 * HALO * HS + q] = Cc;
-      }
-    }
-    __syncthreads();
-    float g[3][VSEG];
-    const auto fid = [](float a, float b) { return a; };
-    row_pass<HALO, HS, LT, BHRUN>(pa, nullptr, hb[0], win, fid);
-    __syncthreads();
-    col_pass<LT, VSEG>(hb[0], win, col, r0, true, g[0]);
-    pin(g[0]);
-    row_pass<HALO, HS, LT, BHRUN>(pa + HALO * HS, nullptr, hb[1], win, fid);
-    __syncthreads();
-    col_pass<LT, VSEG>(hb[1], win, col, r0, true, g[1]);
-    pin(g[1]);
-    row_pass<HALO, HS, LT, BHRUN>(pa + 2 * HALO * HS, nullptr, hb[0], win, fid);
-    __syncthreads();
-    col_pass<LT, VSEG>(hb[0], win, col, r0, true, g[2]);
-    pin(g[2]);
-#pragma unroll
-    for (int j = 0; j < VSEG; ++j) {
-      const int px = t.x0 + col, py = t.y0 + r0 + j;
-      if (px < cv.W && py < cv.H) {
-        const size_t p = base + ch * hw + (size_t)py * cv.W + px;
-        const float xv = xs[j], yv = ys[j];
-        const float d = xv - yv;
-        sl1 += fabs((double)d);
-        const float l1 = w_l1 * invN * (float)((d > 0.0f) - (d < 0.0f));
-        grad[p] = l1 - w_dssim * invN * (g[0][j] + 2.0f * xv * g[1][j] + yv * g[2][j]);
-      }
-    }
+  for (int k = 0; k < AHEAD; ++k) {
+    nx[k] = at(xi, off_in);
+    ny[k] = at(yi, off_in);
+    off_in += pitch;
   }
-  const double t1 = block_sum_d(sl1, sh);
-  const double t2 = block_sum_d(sss, sh);
-  if (threadIdx.x == 0) partials[tile] = make_double2(t1, t2);
+  // the maps of the next row of the images, through the first horizontal windows' exchange
+  const auto take = [&](Neighbours<4>& nb) {
+    const float xv = nx[0], yv = ny[0];
+#pragma unroll
+    for (int k = 0; k + 1 < AHEAD; ++k) {
+      nx[k] = nx[k + 1];
+      ny[k] = ny[k + 1];
+    }
+    nx[AHEAD - 1] = at(xi, off_in);
+    ny[AHEAD - 1] = at(yi, off_in);
+    off_in += pitch;
+    const float maps[4] = {xv, yv, __fmaf_rn(xv, xv, yv * yv), xv * yv};
+    window_cols_load<4>(buf[0], maps, nb);
+  };
+  // the gradient row whose sums g are (from the row above the tile's first 2R + 1 on, of
+  // which nothing is stored)
+  float xc = 0.0f, yc = 0.0f;
+  const auto give = [&](const float (&g)[3]) {
+    const float d = xc - yc;
+    sl1 += fabs((double)d);   // (zero where there is no pixel)
+    const float l1 = w_l1 * invN * (float)((d > 0.0f) - (d < 0.0f));
+    __builtin_amdgcn_raw_buffer_store_b32(
+        __float_as_uint(l1 - w_dssim * invN * (g[0] + 2.0f * xc * g[1] + yc * g[2])), go, off_out, 0, 0);
+    off_out += pitch;
+    xc = at(xo, off_out);
+    yc = at(yo, off_out);
+  };
+  // Each of a row's two exchanges overlaps arithmetic of the row before or after: the
+  // images are taken a row ahead, and the second vertical windows lag by a row.
+  float m[4], h1[4], h2[3] = {0.0f, 0.0f, 0.0f}, g[3];
+  const auto row = [&](int u, int i) {   // u = i mod TAPS
+    Neighbours<4> nb1;
+    take(nb1);
+    window_rows<3>((u + TAPS - 1) % TAPS, w, h2, acc2, g);
+    give(g);
+    const int rst = t.y0 - 3 * R + i;                        // the statistics' row
+    const float mx = m[0], my = m[1];
+    // (fused operations written out: the statistics cancel, so their roundings show)
+    const float sxy = __fmaf_rn(-mx, my, m[3]);
+    const float N1 = __fmaf_rn(2.0f * mx, my, kC1), N2 = __fmaf_rn(2.0f, sxy, kC2);
+    const float M2 = __fmaf_rn(mx, mx, my * my);
+    const float D1 = M2 + kC1, D2 = (m[2] - M2) + kC2;
+    // hardware reciprocals (1 ulp): D1, D2 >= C1 > 0
+    const float r1 = __builtin_amdgcn_rcpf(D1), r2 = __builtin_amdgcn_rcpf(D2);
+    const float rden = r1 * r2;
+    const float S = (N1 * N2) * rden;
+    const bool ok = st_ok && rst >= 0 && rst < H, own = st_own && rst >= t.y0 && rst < y_end;
+    const float abc[3] = {ok ? __fmaf_rn(2.0f * my * (N2 - N1), rden, 2.0f * mx * S * (r2 - r1)) : 0.0f,
+                          ok ? -S * r2 : 0.0f, ok ? 2.0f * N1 * rden : 0.0f};
+    sss += own ? (double)S : 0.0;
+    window_cols_sum<4>(w, nb1, h1);
+    Neighbours<3> nb2;
+    window_cols_load<3>(buf[1], abc, nb2);
+    window_rows<4>((u + 1) % TAPS, w, h1, acc1, m);
+    __builtin_amdgcn_sched_barrier(0);   // (the words' sums stay after the rows': 7 % at any size)
+    window_cols_sum<3>(w, nb2, h2);
+  };
+#pragma unroll
+  for (int u = 0; u <= 2 * R; ++u) {
+    Neighbours<4> nb1;
+    take(nb1);
+    window_cols_sum<4>(w, nb1, h1);
+    window_rows<4>(u, w, h1, acc1, m);
+  }
+  for (int i = 2 * R; i < n_in; i += TAPS)   // (rows past n_in, in the last tile of a column, are all outside)
+#pragma unroll
+    for (int u = 0; u < TAPS; ++u) row((2 * R + u) % TAPS, i + u);
+  window_rows<3>((2 * R + TAPS - 1) % TAPS, w, h2, acc2, g);
+  give(g);
+  for (int o = 32; o > 0; o >>= 1) {
+    sl1 += __shfl_xor(sl1, o);
+    sss += __shfl_xor(sss, o);
+  }
+  if (WAVES == 1) {
+    if (lane == 0) partials[part] = make_double2(sl1, sss);
+    return;
+  }
+  if (lane == 0) sums[ch] = make_double2(sl1, sss);
+  __syncthreads();
+  if (threadIdx.x == 0)
+    partials[tile] = make_double2(sums[0].x + sums[1].x + sums[2].x, sums[0].y + sums[1].y + sums[2].y);
 }
 
 // One workgroup per view: the view's tile partials summed in FP64.
 __global__ __launch_bounds__(256) void k_loss_final(const ViewDev* __restrict__ views, LossTiles lt,
-                                                     const double2* __restrict__ partials, float w_l1,
-                                                     float w_dssim, int ssim, double* __restrict__ out) {
+                                                     const double2* __restrict__ partials, int per_tile,
+                                                     float w_l1, float w_dssim, int ssim,
+                                                     double* __restrict__ out) {
   __shared__ double sh[4];
   const int v = blockIdx.x;
   const ViewDev& cv = views[v];
   double a = 0.0, b = 0.0;
-  for (int t = lt.off[v] + threadIdx.x; t < lt.off[v + 1]; t += blockDim.x) {
+  for (int t = per_tile * lt.off[v] + threadIdx.x; t < per_tile * lt.off[v + 1]; t += blockDim.x) {
     const double2 pt = partials[t];
     a += pt.x;
     b += pt.y;
@@ -623,10 +446,53 @@ int loss_tiles(const ViewDev* hviews, int V) {
   return t;
 }
 
+namespace {
+constexpr int kSsimParts = 65536;   // partial sums that always fit (gs_loss_noalloc's array)
+constexpr int kSsimWaves = 1024 * kSsimOccupancy;   // wavefronts the chip holds at once
+
+int64_t ssim_tiles(const ViewDev* hviews, int V, int rows) {
+  int64_t t = 0;
+  for (int v = 0; v < V; ++v)
+    t += (int64_t)((hviews[v].W + SW - 1) / SW) * ((hviews[v].H + rows - 1) / rows);
+  return t;
+}
+
+// Shape of k_ssim's launch: rows of a tile, tiles, and whether a wavefront (one channel)
+// is a workgroup.  A tile of r rows passes over r + 4R, so taller is less work, but all
+// its rows one after the other: the shape is the one whose rounds of as many wavefronts
+// as fit on the chip, times the rows of a round, are fewest.  1296x864 takes 57 us with
+// 34 rows (one round), 64 with 45, 67 with 23; 10.1 Mpix 285 with 89, 331 with 34 or
+// 122; 0.2 Mpix 28 with 12, 33 with 23.  Three wavefronts (the channels) share a
+// workgroup and one sum only where single sums might not fit.
+struct SsimShape {
+  int rows, tiles, parts;
+  bool waves;
+};
+SsimShape ssim_shape(const ViewDev* hviews, int V) {
+  SsimShape best{};
+  double best_cost = 0.0;
+  for (int rows = 12; rows <= 133; rows += TAPS) {   // with 2R more, whole runs of TAPS rows
+    const int64_t t = ssim_tiles(hviews, V, rows);
+    const bool fits = 3 * t <= kSsimParts;
+    if (!fits && rows < LT) continue;   // (from LT rows on there are no more tiles than loss_tiles() counts)
+    const double rounds = (double)((3 * t + kSsimWaves - 1) / kSsimWaves), cost = (rows + 4 * R) * rounds;
+    if (best_cost == 0.0 || cost < best_cost) {
+      best = SsimShape{rows, (int)t, (int)(fits ? 3 * t : t), fits};
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+}  // namespace
+
+int loss_partials(const ViewDev* hviews, int V) {
+  const int t = loss_tiles(hviews, V), p = ssim_shape(hviews, V).parts;
+  return t > p ? t : p;
+}
+
 hipError_t launch_loss_dev(const ViewDev* dviews, const ViewDev* hviews, int V, const float* color,
-                           const float* target, float w_l1, float w_dssim, double* partials, float* aux,
-                           double* loss_out, float* dL_dcolor, hipStream_t s) {
-  // aux NULL: the fused SSIM kernel (no per-pixel scratch)
+                           const float* target, float w_l1, float w_dssim, double* partials, double* loss_out,
+                           float* dL_dcolor, hipStream_t s) {
   Win win;
   double g[TAPS], tot = 0.0;
   for (int k = 0; k < TAPS; ++k) {
@@ -635,29 +501,29 @@ hipError_t launch_loss_dev(const ViewDev* dviews, const ViewDev* hviews, int V, 
     tot += g[k];
   }
   for (int k = 0; k < TAPS; ++k) win.w[k] = (float)(g[k] / tot);
+  const bool ssim = w_dssim != 0.0f;
+  const SsimShape sh = ssim ? ssim_shape(hviews, V) : SsimShape{};
+  const int rows = ssim ? sh.rows : LT, cols = ssim ? SW : LT;
   LossTiles lt{};
   int t = 0;
   for (int v = 0; v < V; ++v) {
     lt.off[v] = t;
-    t += ((hviews[v].W + LT - 1) / LT) * ((hviews[v].H + LT - 1) / LT);
+    t += ((hviews[v].W + cols - 1) / cols) * ((hviews[v].H + rows - 1) / rows);
   }
   lt.off[V] = t;
   double2* part = reinterpret_cast<double2*>(partials);
-  const bool ssim = w_dssim != 0.0f;
-  const dim3 grid(kXcds * xcd_tile_chunk(t));   // >= t workgroups, see xcd_tile
-  if (!ssim) {
+  const dim3 grid(kXcds * xcd_tile_chunk(ssim ? sh.parts : t));   // at least as many workgroups, see xcd_tile
+  if (!ssim)
     hipLaunchKernelGGL(k_l1, grid, dim3(256), 0, s, dviews, V, lt, color, target, w_l1, dL_dcolor, part);
-  } else if (!aux) {
-    hipLaunchKernelGGL(k_ssim_fused, grid, dim3(256), 0, s, dviews, V, lt, color, target, win, w_l1, w_dssim,
+  else if (sh.waves)
+    hipLaunchKernelGGL(k_ssim<1>, grid, dim3(64), 0, s, dviews, V, lt, rows, color, target, win, w_l1, w_dssim,
                        dL_dcolor, part);
-  } else {
-    hipLaunchKernelGGL(k_ssim_fwd, grid, dim3(256), 0, s, dviews, V, lt, color, target, aux, win, part);
-    hipLaunchKernelGGL(k_ssim_bwd, grid, dim3(256), 0, s, dviews, V, lt, color, target, aux, win, w_l1, w_dssim,
-                       dL_dcolor);
-  }
+  else
+    hipLaunchKernelGGL(k_ssim<3>, grid, dim3(192), 0, s, dviews, V, lt, rows, color, target, win, w_l1, w_dssim,
+                       dL_dcolor, part);
   if (loss_out)
-    hipLaunchKernelGGL(k_loss_final, dim3(V), dim3(256), 0, s, dviews, lt, part, w_l1, w_dssim, ssim ? 1 : 0,
-                       loss_out);
+    hipLaunchKernelGGL(k_loss_final, dim3(V), dim3(256), 0, s, dviews, lt, part, ssim && sh.waves ? 3 : 1, w_l1,
+                       w_dssim, ssim ? 1 : 0, loss_out);
   return hipGetLastError();
 }
 

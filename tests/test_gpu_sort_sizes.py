@@ -1,8 +1,7 @@
 """The binning's sorts at the sizes where their shape changes: entries around one
 4096-item block, around the 128 blocks up to which a pass adds its table's rows and the
 1024 up to which it adds their chunk sums, tile ids of one, two and three digits, and
-depths whose bit patterns
-span from nothing to the whole range of positive floats.  Every listed pair is
+depths whose bit patterns span from nothing to the whole range of positive floats.  Every listed pair is
 enumerated in numpy from the projection's tile rects and ordered by (tile, depth,
 index); keys, values, views and ranges must be equal bit for bit."""
 import numpy as np
