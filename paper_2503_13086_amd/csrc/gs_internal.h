@@ -60,39 +60,34 @@ struct CutoffGeo {
   double u, w, a, b, c, nbc, nba, lim;
 };
 
-__device__ inline CutoffGeo cutoff_geo(const Record& r) {
-#pragma clang fp contract(off)
-  CutoffGeo g;
-  g.u = r.u;
-  g.w = r.w;
-  g.a = r.a;
-  g.b = r.b;
-  g.c = r.c;
-  g.nbc = -g.b / g.c;
-  g.nba = -g.b / g.a;
-  g.lim = -2.0 * (double)r.tau;
-  return g;
-}
-
-// What the fp32 clear-case test reads (40 bytes instead of 64): the centre in FP64,
-// the rest as the fp32 roundings of the FP64 values of cutoff_geo.
-struct CutoffGeoF {
-  double u, w;
-  float a, b, c, nbc, nba, lim;
+// What the fp32 clear-case test reads: the centre of the rect's first pixel less the
+// splat's, in whole pixels (xi, yi) and the rest in [0, 1) (xf, yf), the last column and
+// row of the image in the same whole pixels, and fp32 values of the conic and cutoff.
+struct alignas(16) CutoffBox {
+  float xi, xf, xmax, a;
+  float yi, yf, ymax, b2;   // b2 = 2 b
+  float c, nbc, nba, lim;
 };
 
-__device__ inline CutoffGeoF cutoff_geo_f(const Record& r) {
-  const CutoffGeo g = cutoff_geo(r);
-  CutoffGeoF f;
-  f.u = g.u;
-  f.w = g.w;
-  f.a = (float)g.a;
-  f.b = (float)g.b;
-  f.c = (float)g.c;
-  f.nbc = (float)g.nbc;
-  f.nba = (float)g.nba;
-  f.lim = (float)g.lim;
-  return f;
+// ox, oy: the tile the rect begins with; T: tile edge; W, H: the view's size.
+__device__ inline CutoffBox cutoff_box(const Record& r, int ox, int oy, int T, int W, int H) {
+#pragma clang fp contract(off)
+  const double bx = ((double)(ox * T) + 0.5) - r.u, by = ((double)(oy * T) + 0.5) - r.w;
+  const double fx = floor(bx), fy = floor(by);
+  CutoffBox g;
+  g.xi = (float)fx;
+  g.xf = (float)(bx - fx);
+  g.xmax = g.xi + (float)(W - 1 - ox * T);
+  g.yi = (float)fy;
+  g.yf = (float)(by - fy);
+  g.ymax = g.yi + (float)(H - 1 - oy * T);
+  g.a = r.a;
+  g.b2 = 2.0f * r.b;
+  g.c = r.c;
+  g.nbc = -r.b / r.c;
+  g.nba = -r.b / r.a;
+  g.lim = -2.0f * r.tau;
+  return g;
 }
 
 __device__ inline double cutoff_qform(double a, double b, double c, double dx, double dy) {
@@ -114,33 +109,32 @@ __device__ inline bool tile_meets_cutoff(const CutoffGeo& g, int gx, int gy, int
   return best <= g.lim;
 }
 // The same decision in fp32 where it is clear: 1 keep, 0 drop, -1 too close to call
-// (then tile_meets_cutoff on the FP64 conic and cutoff decides).  The box offsets
-// are taken in FP64 and rounded (signs, hence the inside test, exact); the four edge
-// minima are evaluated at the same clamp points in fp32.  Against the FP64 value
-// on the FP64 conic, rounding of the offsets, the products and the clamp points
-// stays below 8 ulp of S, S = (|a| + |b|) Dx^2 + (|b| + |c|) Dy^2 bounding
-// |a dx^2| + 2 |b dx dy| + |c dy^2| over the box (Dx, Dy the largest offsets), and
-// the record's fp32 copies of a, b, c and the cutoff add at most 2^-24 S and
+// (then tile_meets_cutoff on the FP64 conic and cutoff decides).  tx, ty: the tile's
+// column and row in the rect; T: tile edge.  The quadratic form is convex with its
+// minimum at the splat's centre, so its minimum over the box lies on an edge that faces
+// the centre: at the column ex and row ey of the box nearest to the centre, each with
+// the other coordinate's best value along it (both 0, and the form too, when the box
+// holds the centre).  Box offsets are whole numbers plus one rounded fraction, within
+// 3 ulp and 2^-25; rounding of them, of the products and of the clamp points stays
+// below 10 ulp of S = (|a| + |b|) Dx^2 + (|b| + |c|) Dy^2, which bounds
+// |a dx^2| + 2 |b dx dy| + |c dy^2| over the box (Dx, Dy the largest offsets, at least
+// 1/2), and the record's fp32 copies of a, b, c and the cutoff add at most 2^-24 S and
 // 2^-23 |lim|; a result within 1e-5 S + 1e-6 |lim| of the limit is left undecided.
-__device__ inline int tile_cutoff_fast(const CutoffGeoF& g, int gx, int gy, int T, int W, int H) {
+__device__ inline int tile_cutoff_fast(const CutoffBox& g, float tx, float ty, float T) {
 #pragma clang fp contract(off)
-  const float dx0 = (float)(((double)(gx * T) + 0.5) - g.u);
-  const float dx1 = (float)(fmin((double)(gx * T) + ((double)T - 0.5), (double)W - 0.5) - g.u);
-  const float dy0 = (float)(((double)(gy * T) + 0.5) - g.w);
-  const float dy1 = (float)(fmin((double)(gy * T) + ((double)T - 0.5), (double)H - 0.5) - g.w);
-  if (dx0 <= 0.0f && dx1 >= 0.0f && dy0 <= 0.0f && dy1 >= 0.0f) return g.lim >= 0.0f ? 1 : 0;   // best = 0
-  const float a = g.a, b = g.b, c = g.c, nbc = g.nbc, nba = g.nba;
-  auto q = [&](float dx, float dy) { return ((a * dx) * dx + ((2.0f * b) * dx) * dy) + (c * dy) * dy; };
-  float best = q(dx0, __builtin_amdgcn_fmed3f(nbc * dx0, dy0, dy1));
-  best = fminf(best, q(dx1, __builtin_amdgcn_fmed3f(nbc * dx1, dy0, dy1)));
-  best = fminf(best, q(__builtin_amdgcn_fmed3f(nba * dy0, dx0, dx1), dy0));
-  best = fminf(best, q(__builtin_amdgcn_fmed3f(nba * dy1, dx0, dx1), dy1));
-  const float Dx = fmaxf(fabsf(dx0), fabsf(dx1)), Dy = fmaxf(fabsf(dy0), fabsf(dy1));
-  const float S = (fabsf(a) + fabsf(b)) * (Dx * Dx) + (fabsf(b) + fabsf(c)) * (Dy * Dy);
-  const float lim = g.lim;
-  const float margin = 1e-5f * S + 1e-6f * fabsf(lim) + 1e-30f;
-  if (best <= lim - margin) return 1;
-  if (best > lim + margin) return 0;
+  const float x0 = __fmaf_rn(tx, T, g.xi), y0 = __fmaf_rn(ty, T, g.yi);
+  const float dx0 = x0 + g.xf, dx1 = fminf(x0 + (T - 1.0f), g.xmax) + g.xf;
+  const float dy0 = y0 + g.yf, dy1 = fminf(y0 + (T - 1.0f), g.ymax) + g.yf;
+  const float ex = __builtin_amdgcn_fmed3f(0.0f, dx0, dx1), ey = __builtin_amdgcn_fmed3f(0.0f, dy0, dy1);
+  const float py = __builtin_amdgcn_fmed3f(g.nbc * ex, dy0, dy1), px = __builtin_amdgcn_fmed3f(g.nba * ey, dx0, dx1);
+  const auto q = [&](float dx, float dy) { return __fmaf_rn(dx, __fmaf_rn(g.a, dx, g.b2 * dy), (g.c * dy) * dy); };
+  const float best = fminf(q(ex, py), q(px, ey));
+  const float Dx = fmaxf(fmaxf(fabsf(dx0), fabsf(dx1)), 0.5f), Dy = fmaxf(fmaxf(fabsf(dy0), fabsf(dy1)), 0.5f);
+  const float ab = __fmaf_rn(fabsf(g.b2), 0.5f, fabsf(g.a)), bc = __fmaf_rn(fabsf(g.b2), 0.5f, fabsf(g.c));
+  const float S = __fmaf_rn(ab, Dx * Dx, bc * (Dy * Dy));
+  const float margin = __fmaf_rn(1e-5f, S, __fmaf_rn(1e-6f, fabsf(g.lim), 1e-30f));
+  if (best <= g.lim - margin) return 1;
+  if (best > g.lim + margin) return 0;
   return -1;
 }
 

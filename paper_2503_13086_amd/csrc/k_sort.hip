@@ -589,16 +589,25 @@ __device__ inline int round_owner(uint32_t excl, uint32_t cand, uint32_t cb, int
   return o < 0 ? 0 : o;   // only lanes past the last candidate could see no mark
 }
 
-// (tile column, row) offsets of candidate `local` in a rect nx tiles wide: the
-// quotient from the hardware reciprocal (within one of the true one for the
-// counts here, below 2^24), then corrected.
-__device__ inline void rect_cell(uint32_t local, uint32_t nx, uint32_t& tx, uint32_t& ty) {
-  ty = (uint32_t)((float)local * __builtin_amdgcn_rcpf((float)nx));
-  if (ty * nx > local) --ty;
-  else if ((ty + 1) * nx <= local) ++ty;
-  tx = local - ty * nx;
+// Column and row (whole numbers) of candidate `local` in a rect nx tiles wide, rn its
+// hardware reciprocal: (local + 1/2) / nx is 1 / (2 nx) or more from a whole number,
+// which the quotient's 2^-22 stays within up to 2^21 candidates; `many` (uniform)
+// corrects it for more (below 2^24).
+__device__ inline void rect_cell(uint32_t local, float nx, float rn, bool many, float& tx, float& ty) {
+  const float l = (float)local;
+  ty = floorf((l + 0.5f) * rn);
+  tx = __fmaf_rn(-ty, nx, l);
+  if (many) {
+    if (tx < 0.0f) {
+      ty -= 1.0f;
+      tx += nx;
+    } else if (tx >= nx) {
+      ty += 1.0f;
+      tx -= nx;
+    }
+  }
 }
-
+constexpr uint32_t kManyCells = 1u << 21;
 
 // Wave-wide counter update: lane 0 adds `total` to *ctr; every lane gets the old
 // value (0 and no update when total is 0).
@@ -623,7 +632,10 @@ __device__ inline uint32_t split_threshold(uint32_t cand) {
 // Kept pairs per entry (index order, coalesced reads): the tiles of the entry's
 // rect whose pixel-centre box meets its cutoff region.  The wave's candidates are
 // spread over its lanes; runs of one entry within 64 candidates are counted with
-// ballots by the run's first lane.  Each entry also gets a 16-byte EmitInfo: its
+// ballots by the run's first lane.  Bound by vector instructions (0.32 per SIMD
+// and cycle): the box offsets as whole numbers plus a fraction in fp32 and two edges in
+// place of four FP64 offsets and four edges take 180 us where 277 were taken for
+// 1 000 000 Gaussians in nine views, 65 where 75 for 2 500 000 in one.  Each entry also gets a 16-byte EmitInfo: its
 // rect and, when it has at most 64 candidates, the outcome of every test (bit i
 // for the rect's i-th tile, row-major), which is all emission then has to fetch.
 constexpr uint32_t kRedoMark = 1u << 31;
@@ -637,13 +649,11 @@ __global__ __launch_bounds__(kThreads) void k_count_kept(const uint32_t* __restr
                                                           uint32_t* __restrict__ redo_list,
                                                           uint2* __restrict__ items, size_t icap) {
   __shared__ uint32_t s_cp[kWaves][65];
-  __shared__ uint32_t s_nx[kWaves][64];
-  __shared__ uint32_t s_org[kWaves][64];    // rect origin (tx0 | ty0 << 16)
-  __shared__ uint32_t s_wh[kWaves][64];     // view size (W | H << 16)
+  __shared__ float2 s_nx[kWaves][64];       // rect width in tiles and its reciprocal
   __shared__ uint32_t s_k[kWaves][64];
   __shared__ uint64_t s_bits[kWaves][64];
   __shared__ int s_own[kWaves][64];
-  __shared__ CutoffGeoF s_geo[kWaves][64];    // fp32 clear-case geometry
+  __shared__ CutoffBox s_geo[kWaves][64];     // fp32 clear-case geometry
   const int w = threadIdx.x / 64;
   const unsigned lane = __lane_id();
   const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -680,10 +690,9 @@ __global__ __launch_bounds__(kThreads) void k_count_kept(const uint32_t* __restr
   s_bits[w][lane] = 0ull;
   if (cand) {
     const ViewDev& cv = views[e / (size_t)n];
-    s_nx[w][lane] = (uint32_t)(rc.y - rc.x + 1);
-    s_org[w][lane] = (uint32_t)rc.x | ((uint32_t)rc.z << 16);
-    s_wh[w][lane] = (uint32_t)cv.W | ((uint32_t)cv.H << 16);
-    s_geo[w][lane] = cutoff_geo_f(rec[e]);
+    const float nx = (float)(rc.y - rc.x + 1);
+    s_nx[w][lane] = make_float2(nx, __builtin_amdgcn_rcpf(nx));
+    s_geo[w][lane] = cutoff_box(rec[e], rc.x, rc.z, T, cv.W, cv.H);
   }
   __builtin_amdgcn_wave_barrier();
   const uint32_t C = s_cp[w][64];
@@ -699,12 +708,10 @@ __global__ __launch_bounds__(kThreads) void k_count_kept(const uint32_t* __restr
       lo = owner;
       const uint32_t li = q - s_cp[w][lo];
       first = lane == 0 || li == 0u;          // this lane opens its entry's run in the round
-      uint32_t tx, ty;
-      rect_cell(li, s_nx[w][lo], tx, ty);
-      const uint32_t org = s_org[w][lo], wh = s_wh[w][lo];
-      const int gx = (int)((org & 0xffffu) + tx), gy = (int)((org >> 16) + ty);
-      const int W = (int)(wh & 0xffffu), H = (int)(wh >> 16);
-      const int fast = exact_all ? -1 : tile_cutoff_fast(s_geo[w][lo], gx, gy, T, W, H);
+      float tx, ty;
+      const float2 nx = s_nx[w][lo];
+      rect_cell(li, nx.x, nx.y, C > kManyCells, tx, ty);
+      const int fast = exact_all ? -1 : tile_cutoff_fast(s_geo[w][lo], tx, ty, (float)T);
       pass = fast > 0;
       undecided = fast < 0;   // decided by the exact pass
     }
@@ -757,7 +764,7 @@ __global__ __launch_bounds__(kThreads) void k_count_chunks(const ushort4* __rest
     const uint32_t e = it.x;
     const ushort4 rc = rect[e];
     const ViewDev& cv = views[e / (uint32_t)n];
-    const CutoffGeoF geo = cutoff_geo_f(rec[e]);
+    const CutoffBox geo = cutoff_box(rec[e], rc.x, rc.z, T, cv.W, cv.H);
     const uint32_t nx = (uint32_t)(rc.y - rc.x + 1), C = nx * (uint32_t)(rc.w - rc.z + 1);
     const uint32_t c1 = it.y + kChunk < C ? it.y + kChunk : C;
     uint32_t k = 0;
@@ -766,9 +773,9 @@ __global__ __launch_bounds__(kThreads) void k_count_chunks(const ushort4* __rest
       const uint32_t li = cb + lane;
       int f = 0;
       if (li < c1) {
-        uint32_t tx, ty;
-        rect_cell(li, nx, tx, ty);
-        f = tile_cutoff_fast(geo, (int)(rc.x + tx), (int)(rc.z + ty), T, cv.W, cv.H);
+        float tx, ty;
+        rect_cell(li, (float)nx, __builtin_amdgcn_rcpf((float)nx), C > kManyCells, tx, ty);
+        f = tile_cutoff_fast(geo, tx, ty, (float)T);
       }
       k += (uint32_t)__popcll(__ballot(f > 0));
       undecided |= __ballot(f < 0) != 0ull;
@@ -805,8 +812,8 @@ __global__ __launch_bounds__(kThreads) void k_count_redo(const uint32_t* __restr
     const int g = (int)(e - (uint32_t)v * (uint32_t)n);
     const ViewDev& cv = views[v];
     const CutoffGeo ex = exact_cutoff_geo(P, stride, g, cv);
-    const CutoffGeoF fg = cutoff_geo_f(rec[e]);
     const ushort4 rc = rect[e];
+    const CutoffBox fg = cutoff_box(rec[e], rc.x, rc.z, T, cv.W, cv.H);
     const uint32_t nx = (uint32_t)(rc.y - rc.x + 1), C = touched[e];
     const bool large = C > 64u;
     size_t off = 0;
@@ -832,7 +839,7 @@ __global__ __launch_bounds__(kThreads) void k_count_redo(const uint32_t* __restr
       if (li < C) {
         const uint32_t ty = li / nx, tx = li - ty * nx;
         const int gx = (int)(rc.x + tx), gy = (int)(rc.z + ty);
-        const int f = exact_all ? -1 : tile_cutoff_fast(fg, gx, gy, T, cv.W, cv.H);
+        const int f = exact_all ? -1 : tile_cutoff_fast(fg, (float)tx, (float)ty, (float)T);
         keep = f >= 0 ? f != 0 : tile_meets_cutoff(ex, gx, gy, T, cv.W, cv.H);
       }
       const uint64_t m = __ballot(keep);
@@ -890,14 +897,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
   __shared__ uint32_t s_dpre[kWaves][64];   // pairs of the wave's split entries before each entry
   __shared__ uint32_t s_rid[kWaves][64];
   __shared__ uint32_t s_base[kWaves][64];   // global tile id of the rect's first tile
-  __shared__ uint32_t s_nx[kWaves][64];     // rect width in tiles
+  __shared__ float2 s_nx[kWaves][64];       // rect width in tiles and its reciprocal
   __shared__ uint32_t s_tx[kWaves][64];     // tiles per row of the entry's view
-  __shared__ uint32_t s_org[kWaves][64];    // rect origin (tx0 | ty0 << 16)
-  __shared__ uint32_t s_wh[kWaves][64];     // view size (W | H << 16)
   __shared__ uint64_t s_bits[kWaves][64];   // test outcomes (entries of <= 64 candidates)
   __shared__ int s_own[kWaves][64];         // round_owner scratch
   __shared__ int s_slot[kWaves][64];        // entry's s_geo slot (-1: none)
-  __shared__ CutoffGeoF s_geo[kWaves][kEmitGeoSlots];
+  __shared__ CutoffBox s_geo[kWaves][kEmitGeoSlots];
   const int w = threadIdx.x / 64;
   const unsigned lane = __lane_id();
   const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -992,14 +997,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
   if (cand) {
     const ViewDev& cv = views[rid / (uint32_t)n];
     s_base[w][lane] = (uint32_t)cv.tile_off + (uint32_t)rc.z * (uint32_t)cv.tiles_x + rc.x;
-    s_nx[w][lane] = (uint32_t)(rc.y - rc.x + 1);
+    const float nx = (float)(rc.y - rc.x + 1);
+    s_nx[w][lane] = make_float2(nx, __builtin_amdgcn_rcpf(nx));
     s_tx[w][lane] = (uint32_t)cv.tiles_x;
     if (cull) {
       s_bits[w][lane] = bits;
       if (large) {
-        s_org[w][lane] = (uint32_t)rc.x | ((uint32_t)rc.z << 16);
-        s_wh[w][lane] = (uint32_t)cv.W | ((uint32_t)cv.H << 16);
-        if (slot < kEmitGeoSlots) s_geo[w][slot] = cutoff_geo_f(rec[rid]);
+        if (slot < kEmitGeoSlots) s_geo[w][slot] = cutoff_box(rec[rid], rc.x, rc.z, T, cv.W, cv.H);
       }
     }
   }
@@ -1016,9 +1020,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
     carry = __builtin_amdgcn_readlane(owner, 63);
     if (q < C) {
       const int lo = owner;
-      uint32_t tx, ty;
-      rect_cell(q - s_cp[w][lo], s_nx[w][lo], tx, ty);
-      tile = s_base[w][lo] + ty * s_tx[w][lo] + tx;
+      float tx, ty;
+      const float2 nx = s_nx[w][lo];
+      rect_cell(q - s_cp[w][lo], nx.x, nx.y, C > kManyCells, tx, ty);
+      tile = s_base[w][lo] + __umul24((uint32_t)ty, s_tx[w][lo]) + (uint32_t)tx;
       r = s_rid[w][lo];
       keep = true;
       if (cull) {
@@ -1026,7 +1031,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
         if (s_cp[w][lo + 1] - s_cp[w][lo] <= 64u) {
           keep = ((s_bits[w][lo] >> li) & 1ull) != 0ull;
         } else {
-          const uint32_t org = s_org[w][lo], wh = s_wh[w][lo];
           const int sl = s_slot[w][lo];
           const uint64_t ib = s_bits[w][lo];
           if (ib & kRedoFlag) {
@@ -1036,9 +1040,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
             // the fp32 test decided every candidate of this entry in the count (else
             // the exact pass would have stored its outcomes, or reported a full
             // outcome array), and decides them the same way here
-            const CutoffGeoF geo = sl >= 0 ? s_geo[w][sl] : cutoff_geo_f(rec[r]);
-            keep = tile_cutoff_fast(geo, (int)((org & 0xffffu) + tx), (int)((org >> 16) + ty), T,
-                                    (int)(wh & 0xffffu), (int)(wh >> 16)) > 0;
+            CutoffBox geo;
+            if (sl >= 0) {
+              geo = s_geo[w][sl];
+            } else {
+              const ushort4 orc = rect[r];
+              const ViewDev& ov = views[r / (uint32_t)n];
+              geo = cutoff_box(rec[r], orc.x, orc.z, T, ov.W, ov.H);
+            }
+            keep = tile_cutoff_fast(geo, tx, ty, (float)T) > 0;
           }
         }
       }
@@ -1094,8 +1104,8 @@ __global__ __launch_bounds__(kThreads) void k_emit_chunks(SplitEntry* __restrict
     }
     const ViewDev& cv = views[rid / (uint32_t)n];
     const bool stored = (ib & kRedoFlag) != 0ull;
-    CutoffGeoF geo{};
-    if (cull && !stored) geo = cutoff_geo_f(rec[rid]);
+    CutoffBox geo{};
+    if (cull && !stored) geo = cutoff_box(rec[rid], rc.x, rc.z, T, cv.W, cv.H);
     const uint32_t nx = (uint32_t)(rc.y - rc.x + 1), C = nx * (uint32_t)(rc.w - rc.z + 1);
     const uint32_t c1 = it.y + kChunk < C ? it.y + kChunk : C;
     const uint32_t tile0 = (uint32_t)cv.tile_off + (uint32_t)rc.z * (uint32_t)cv.tiles_x + rc.x;
@@ -1108,13 +1118,13 @@ __global__ __launch_bounds__(kThreads) void k_emit_chunks(SplitEntry* __restrict
       bool keep = false;
       tl[r] = 0;
       if (li < c1) {
-        uint32_t tx, ty;
-        rect_cell(li, nx, tx, ty);
-        tl[r] = tile0 + ty * (uint32_t)cv.tiles_x + tx;
+        float tx, ty;
+        rect_cell(li, (float)nx, __builtin_amdgcn_rcpf((float)nx), C > kManyCells, tx, ty);
+        tl[r] = tile0 + __umul24((uint32_t)ty, (uint32_t)cv.tiles_x) + (uint32_t)tx;
         keep = true;
         if (cull) {
           keep = stored ? ((redo_bits[(size_t)(ib & ~kRedoFlag) + li / 32u] >> (li & 31u)) & 1u) != 0u
-                        : tile_cutoff_fast(geo, (int)(rc.x + tx), (int)(rc.z + ty), T, cv.W, cv.H) > 0;
+                        : tile_cutoff_fast(geo, tx, ty, (float)T) > 0;
         }
       }
       m[r] = __ballot(keep);
