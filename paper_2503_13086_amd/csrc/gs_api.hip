@@ -86,7 +86,6 @@ struct gs_ctx {
   bool load_pending = false;   // dG holds a load-balancing gradient for the current forward
   ViewDev* h_views = nullptr;
   bool views_valid = false;   // the device views equal hviews
-  unsigned long long* h_total = nullptr;
   hipEvent_t views_ev = nullptr;
   bool views_ev_pending = false;
   hipEvent_t status_ev = nullptr;  // recorded after the binning's check wrote the mirror
@@ -316,10 +315,12 @@ gs_status gs_create(gs_ctx** out, int32_t device) {
   if (hipSetDevice(device) != hipSuccess) return GS_ERR_HIP;
   gs_ctx* c = new gs_ctx();
   c->device = device;
-  if (hipHostMalloc((void**)&c->h_views, sizeof(ViewDev) * GS_MAX_VIEWS, hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc((void**)&c->h_total, sizeof(unsigned long long), hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc((void**)&c->h_status, sizeof(DevStatus), hipHostMallocMapped | hipHostMallocCoherent) !=
-          hipSuccess ||
+  // one pinned allocation for the status mirror and the views (each costs tens of
+  // microseconds, and autograd makes a context per call)
+  constexpr size_t kViewsAt = 256;
+  static_assert(sizeof(DevStatus) <= kViewsAt, "the views follow the mirror");
+  if (hipHostMalloc((void**)&c->h_status, kViewsAt + sizeof(ViewDev) * GS_MAX_VIEWS,
+                    hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
       hipHostGetDevicePointer((void**)&c->d_mirror, c->h_status, 0) != hipSuccess ||
       hipEventCreateWithFlags(&c->views_ev, hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&c->status_ev, hipEventDisableTiming) != hipSuccess ||
@@ -331,6 +332,7 @@ gs_status gs_create(gs_ctx** out, int32_t device) {
   }
   c->status.cap = kStatusAllocBytes;
   std::memset(c->h_status, 0, sizeof(DevStatus));
+  c->h_views = reinterpret_cast<ViewDev*>(reinterpret_cast<char*>(c->h_status) + kViewsAt);
   *out = c;
   return GS_OK;
 }
@@ -341,8 +343,6 @@ void gs_destroy(gs_ctx* c) {
   (void)hipDeviceSynchronize();
   for (DevBuf* b : all_bufs(c))
     if (b->p) (void)hipFree(b->p);
-  if (c->h_views) (void)hipHostFree(c->h_views);
-  if (c->h_total) (void)hipHostFree(c->h_total);
   if (c->h_status) (void)hipHostFree(c->h_status);
   if (c->views_ev) (void)hipEventDestroy(c->views_ev);
   if (c->status_ev) (void)hipEventDestroy(c->status_ev);
@@ -522,9 +522,8 @@ gs_status gs_bin_sort(gs_ctx* c, int64_t* n_pairs_out, gs_stream stream) {
   }
   c->K_known = false;
   if (wait) {
-    GS_HIP(c, hipMemcpyAsync(c->h_total, &dst->n_pairs, 8, hipMemcpyDeviceToHost, s));
-    GS_HIP(c, hipStreamSynchronize(s));
-    const uint64_t K = *c->h_total;
+    GS_HIP(c, hipStreamSynchronize(s));   // (the scan wrote K to the host mirror: no copy behind it)
+    const uint64_t K = c->h_status->n_pairs;
     if (K >= (1ull << 32)) return fail(c, GS_ERR_CAPACITY, "more than 2^32 - 1 (tile, Gaussian) pairs");
     c->K = K;
     c->K_known = true;
