@@ -512,7 +512,8 @@ gs_status gs_bin_sort(gs_ctx* c, int64_t* n_pairs_out, gs_stream stream) {
     Prof pr(c, GS_K_SCAN, s);
     // with a wait the buffers grow to K before anything reads them: no cap here
     GS_HIP(c, launch_scan_touched(order, packed ? 1 : 0, per_entry, NV, c->groupsums.as<uint32_t>(),
-                                  c->blocksums.as<uint32_t>(), dst, c->d_mirror, wait ? ~0ull : c->pair_cap, s));
+                                  c->blocksums.as<uint32_t>(), dst, c->d_mirror, wait ? ~0ull : c->pair_cap,
+                                  c->ranges.as<uint2>(), c->n_tiles, s));
   }
   if (!cap) {
     GS_HIP(c, hipEventRecord(c->status_ev, s));

@@ -145,7 +145,7 @@ __host__ __device__ inline int n_params(int D) { return 11 + 3 * n_sh(D); }
 // start of every binning.
 struct DevStatus {
   int32_t code;                   // GS_OK or the first error (GS_ERR_CAPACITY)
-  uint32_t pad;
+  uint32_t scan_done;             // workgroups of the scan's first kernel that have finished
   unsigned long long n_pairs;     // pairs of the last binning (K)
   unsigned long long n_eff;       // K when the pair buffers hold it, else 0: the later kernels then do nothing
   unsigned long long need_pairs;  // pairs the last binning needed room for
@@ -159,7 +159,7 @@ constexpr uint64_t kRedoFlag = 1ull << 63;
 
 __device__ inline void status_clear(DevStatus* st) {
   st->code = GS_OK;
-  st->pad = 0u;
+  st->scan_done = 0u;
   st->n_pairs = 0ull;
   st->n_eff = 0ull;
   st->need_pairs = 0ull;
@@ -213,12 +213,13 @@ constexpr uint32_t kPackRidMask = 0x00ffffffu;
 // st->n_pairs and is checked against the pair capacity: n_eff = K if K <= cap, K <
 // 2^32 and no earlier failure, else 0 (GS_ERR_CAPACITY with need_pairs = K when K
 // does not fit); then the status is copied to `mirror` (host-visible memory).
-// (packed != 0: order entries come from radix_sort_depth with counts)
+// (packed != 0: order entries come from radix_sort_depth with counts.)  Also clears
+// ranges[0, n_tiles) for launch_ranges.
 size_t scan_block_words(size_t n);
 inline size_t scan_group_words(size_t n) { return (n + 63) / 64; }
 hipError_t launch_scan_touched(const uint32_t* order, int packed, const uint32_t* touched, size_t n,
                                uint32_t* group_sums, uint32_t* block_sums, DevStatus* st, DevStatus* mirror,
-                               unsigned long long cap, hipStream_t s);
+                               unsigned long long cap, uint2* ranges, int n_tiles, hipStream_t s);
 // kept[e] = tiles of entry e's rect whose pixel-centre box meets its cutoff region
 // (entries in index order; rect tile count in touched)
 // What emission fetches per culled entry: its tile rect and, for rects of at most

@@ -468,15 +468,92 @@ __device__ inline uint32_t entry_count(uint32_t o, int packed, const uint32_t* _
   return c == kPackSat ? touched[o & kPackRidMask] : c;
 }
 
+// The binning's capacity check on the total K (one thread, once every block sum is
+// in), which also copies the status into the host-visible mirror; the host reads it
+// once the stream has passed this point.
+__device__ inline void check_pairs(DevStatus* __restrict__ st, DevStatus* __restrict__ mirror,
+                                   unsigned long long K, unsigned long long cap) {
+  st->n_pairs = K;
+  if (K > cap || K >= (1ull << 32)) {
+    st->n_eff = 0ull;
+    st->need_pairs = K;
+    status_fail(st, GS_ERR_CAPACITY);
+  } else {
+    // an earlier failure (the exact pass's outcome store too small) leaves counts
+    // the emission could not reproduce: then no pair is emitted either
+    st->n_eff = st->code == GS_OK ? K : 0ull;
+  }
+  mirror->n_pairs = K;
+  mirror->n_eff = st->n_eff;
+  mirror->need_pairs = st->need_pairs;
+  mirror->redo_count = st->redo_count;
+  mirror->redo_words = st->redo_words;
+  mirror->need_redo = st->need_redo;
+  mirror->scan_done = 0u;
+  __threadfence_system();
+  mirror->code = st->code;
+}
+
+// Exclusive scan of the block sums in 64 bits by one workgroup of THREADS threads, then
+// the check on the total.  The sums are read past this XCD's L2 (others wrote them).
+template <int THREADS>
+__device__ inline void scan_blocks(uint32_t* __restrict__ block_sums, int nb, DevStatus* __restrict__ st,
+                                   DevStatus* __restrict__ mirror, unsigned long long cap) {
+  __shared__ unsigned long long wsum[THREADS / 64];
+  __shared__ unsigned long long carry;
+  if (threadIdx.x == 0) carry = 0;
+  __syncthreads();
+  for (int b0 = 0; b0 < nb; b0 += THREADS) {
+    const int b = b0 + threadIdx.x;
+    const unsigned long long x =
+        b < nb ? __hip_atomic_load(block_sums + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    unsigned long long incl = x;
+    for (int off = 1; off < 64; off <<= 1) {
+      const unsigned long long y = __shfl_up(incl, off);
+      if ((int)__lane_id() >= off) incl += y;
+    }
+    if (__lane_id() == 63) wsum[threadIdx.x / 64] = incl;
+    __syncthreads();
+    unsigned long long wpre = 0;
+    for (int w = 0; w < (int)(threadIdx.x / 64); ++w) wpre += wsum[w];
+    const unsigned long long c = carry;
+    if (b < nb) block_sums[b] = (uint32_t)(c + wpre + incl - x);   // offsets < 2^32 checked on the host
+    __syncthreads();
+    if (threadIdx.x == THREADS - 1) carry = c + wpre + incl;
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) check_pairs(st, mirror, carry, cap);
+}
+
+__global__ __launch_bounds__(1024) void k_scan_blocks(uint32_t* __restrict__ block_sums, int nb,
+                                                       DevStatus* __restrict__ st, DevStatus* __restrict__ mirror,
+                                                       unsigned long long cap) {
+  scan_blocks<1024>(block_sums, nb, st, mirror, cap);
+}
+
+// Up to so many blocks the last workgroup of k_scan_reduce to finish scans their sums
+// itself (a launch less, about 4 us of each binning); beyond it k_scan_blocks does, with
+// its 1024 threads.
+constexpr int kLastBlockScan = 256;
+
 // Sums of the counts of every 64 consecutive depth-ordered entries (group_sums,
 // one per wave of the emission) and of every kScanItems entries (block_sums).
 // Thread t takes 16 consecutive entries (four 16-byte loads), four lanes a group.
+// Beside it the tile ranges are cleared for k_ranges (n_clear of them), and the last
+// workgroup scans the sums (at most kLastBlockScan blocks).
 __global__ __launch_bounds__(kThreads) void k_scan_reduce(const uint32_t* __restrict__ order,
                                                            const uint32_t* __restrict__ touched, size_t n,
                                                            int packed, uint32_t* __restrict__ group_sums,
-                                                           uint32_t* __restrict__ block_sums) {
+                                                           uint32_t* __restrict__ block_sums,
+                                                           uint2* __restrict__ ranges, uint32_t n_clear,
+                                                           DevStatus* __restrict__ st,
+                                                           DevStatus* __restrict__ mirror,
+                                                           unsigned long long cap) {
   static_assert(kScanItems == 16 * kThreads, "16 entries per thread");
   __shared__ uint32_t sh[kWaves];
+  __shared__ bool last;
+  for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < n_clear; i += gridDim.x * kThreads)
+    ranges[i] = make_uint2(0u, 0u);
   const size_t e0 = (size_t)blockIdx.x * kScanItems + 16 * (size_t)threadIdx.x;
   uint32_t c = 0;
   if (e0 + 16 <= n) {
@@ -496,63 +573,21 @@ __global__ __launch_bounds__(kThreads) void k_scan_reduce(const uint32_t* __rest
   const bool lead = (threadIdx.x & 3u) == 0u;
   if (lead && e0 < n) group_sums[e0 / 64] = c;
   const uint32_t t = block_sum_u32(lead ? c : 0u, sh);
-  if (threadIdx.x == 0) block_sums[blockIdx.x] = t;
-}
-
-// single workgroup: exclusive scan of block sums in 64-bit, total to *total
-// Besides the scan: the binning's capacity check on the total K (thread 0, once
-// every block sum is in), which also copies the status into the host-visible
-// mirror; the host reads it once the stream has passed this point (see
-// check_pairs).
-__device__ inline void check_pairs(DevStatus* __restrict__ st, DevStatus* __restrict__ mirror,
-                                   unsigned long long K, unsigned long long cap) {
-  st->n_pairs = K;
-  if (K > cap || K >= (1ull << 32)) {
-    st->n_eff = 0ull;
-    st->need_pairs = K;
-    status_fail(st, GS_ERR_CAPACITY);
-  } else {
-    // an earlier failure (the exact pass's outcome store too small) leaves counts
-    // the emission could not reproduce: then no pair is emitted either
-    st->n_eff = st->code == GS_OK ? K : 0ull;
+  const int nb = (int)gridDim.x;
+  if (nb > kLastBlockScan) {
+    if (threadIdx.x == 0) block_sums[blockIdx.x] = t;
+    return;
   }
-  mirror->n_pairs = K;
-  mirror->n_eff = st->n_eff;
-  mirror->need_pairs = st->need_pairs;
-  mirror->redo_count = st->redo_count;
-  mirror->redo_words = st->redo_words;
-  mirror->need_redo = st->need_redo;
-  mirror->pad = 0u;
-  __threadfence_system();
-  mirror->code = st->code;
-}
-
-__global__ __launch_bounds__(1024) void k_scan_blocks(uint32_t* __restrict__ block_sums, int nb,
-                                                       DevStatus* __restrict__ st, DevStatus* __restrict__ mirror,
-                                                       unsigned long long cap) {
-  __shared__ unsigned long long wsum[16];
-  __shared__ unsigned long long carry;
-  if (threadIdx.x == 0) carry = 0;
+  if (threadIdx.x == 0) {
+    // the sum is in memory before the count of finished workgroups says so (the count
+    // begins at 0 with every binning: status_clear)
+    __hip_atomic_store(block_sums + blockIdx.x, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last = __hip_atomic_fetch_add(&st->scan_done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)nb - 1u;
+  }
   __syncthreads();
-  for (int b0 = 0; b0 < nb; b0 += 1024) {
-    const int b = b0 + threadIdx.x;
-    const unsigned long long x = b < nb ? block_sums[b] : 0ull;
-    unsigned long long incl = x;
-    for (int off = 1; off < 64; off <<= 1) {
-      const unsigned long long y = __shfl_up(incl, off);
-      if ((int)__lane_id() >= off) incl += y;
-    }
-    if (__lane_id() == 63) wsum[threadIdx.x / 64] = incl;
-    __syncthreads();
-    unsigned long long wpre = 0;
-    for (int w = 0; w < (int)(threadIdx.x / 64); ++w) wpre += wsum[w];
-    const unsigned long long c = carry;
-    if (b < nb) block_sums[b] = (uint32_t)(c + wpre + incl - x);   // offsets < 2^32 checked on the host
-    __syncthreads();
-    if (threadIdx.x == 1023) carry = c + wpre + incl;
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) check_pairs(st, mirror, carry, cap);
+  if (!last) return;
+  scan_blocks<kThreads>(block_sums, nb, st, mirror, cap);
+  if (threadIdx.x == 0) st->scan_done = 0u;
 }
 
 // Inclusive max over lanes 0..l (DPP: shifts within rows of 16 lanes, then the
@@ -1297,11 +1332,18 @@ size_t scan_block_words(size_t n) { return (n + kScanItems - 1) / kScanItems + 1
 
 hipError_t launch_scan_touched(const uint32_t* order, int packed, const uint32_t* touched, size_t n,
                                uint32_t* group_sums, uint32_t* block_sums, DevStatus* st, DevStatus* mirror,
-                               unsigned long long cap, hipStream_t s) {
+                               unsigned long long cap, uint2* ranges, int n_tiles, hipStream_t s) {
   const int nb = (int)((n + kScanItems - 1) / kScanItems);
+  // the ranges are cleared beside the sums unless that were much of the work
+  const bool beside = (size_t)n_tiles <= (size_t)nb * kThreads * 4;
+  if (!beside) {
+    const hipError_t e = launch_fill_u32(reinterpret_cast<uint32_t*>(ranges), 0u, (size_t)n_tiles * 2, s);
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kThreads), 0, s, order, touched, n, packed, group_sums,
-                     block_sums);
-  hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(1024), 0, s, block_sums, nb, st, mirror, cap);
+                     block_sums, ranges, beside ? (uint32_t)n_tiles : 0u, st, mirror, cap);
+  if (nb > kLastBlockScan)
+    hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(1024), 0, s, block_sums, nb, st, mirror, cap);
   return hipGetLastError();
 }
 
@@ -1364,8 +1406,7 @@ hipError_t launch_status_reset(DevStatus* st, hipStream_t s) {
 
 hipError_t launch_ranges(const uint32_t* pair_tile, size_t K_cap, const unsigned long long* n_dev, uint2* ranges,
                          int n_tiles, hipStream_t s) {
-  hipError_t e = launch_fill_u32(reinterpret_cast<uint32_t*>(ranges), 0u, (size_t)n_tiles * 2, s);
-  if (e != hipSuccess || K_cap == 0) return e;
+  if (K_cap == 0) return hipSuccess;
   const unsigned blocks = (unsigned)((K_cap + 4 * 256 - 1) / (4 * 256));
   hipLaunchKernelGGL(k_ranges, dim3(blocks), dim3(256), 0, s, pair_tile, K_cap, n_dev, ranges, (uint32_t)n_tiles);
   return hipGetLastError();
@@ -1421,6 +1462,7 @@ hipError_t launch_ordered_sum(const uint32_t* pair_rec, size_t K_cap, const unsi
         hipSuccess)
       return e;
   }
+  if ((e = launch_fill_u32(reinterpret_cast<uint32_t*>(eranges), 0u, n_entries * 2, s)) != hipSuccess) return e;
   if ((e = launch_ranges(in_b ? keys_b : keys_a, K_cap, n_dev, eranges, (int)n_entries, s)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_ordered_sum, dim3((unsigned)((n_entries + 255) / 256)), dim3(256), 0, s, eranges,
                      in_b ? vals_b : vals_a, part, grad2d, n_entries);
