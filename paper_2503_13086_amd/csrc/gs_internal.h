@@ -132,7 +132,11 @@ __device__ inline int tile_cutoff_fast(const CutoffBox& g, float tx, float ty, f
   const float Dx = fmaxf(fmaxf(fabsf(dx0), fabsf(dx1)), 0.5f), Dy = fmaxf(fmaxf(fabsf(dy0), fabsf(dy1)), 0.5f);
   const float ab = __fmaf_rn(fabsf(g.b2), 0.5f, fabsf(g.a)), bc = __fmaf_rn(fabsf(g.b2), 0.5f, fabsf(g.c));
   const float S = __fmaf_rn(ab, Dx * Dx, bc * (Dy * Dy));
-  const float margin = __fmaf_rn(1e-5f, S, __fmaf_rn(1e-6f, fabsf(g.lim), 1e-30f));
+  // a box that holds the centre (to 2^-24 of a pixel, where the form is below 1e-14) is
+  // clear whatever S is: splats just below the cutoff opacity, which training leaves by
+  // the thousand, have nothing but such boxes
+  const bool holds = fmaxf(fabsf(ex), fabsf(ey)) == 0.0f;
+  const float margin = holds ? 1e-9f : __fmaf_rn(1e-5f, S, __fmaf_rn(1e-6f, fabsf(g.lim), 1e-30f));
   if (best <= g.lim - margin) return 1;
   if (best > g.lim + margin) return 0;
   return -1;
