@@ -374,11 +374,12 @@ __global__ __launch_bounds__(T * T) void k_render_count(const ViewDev* __restric
   if (tile >= n_tiles_total) return;
   const TileGeom tg = tile_geom<T>(views, V, tile);
   const uint2 rg = ranges[tile];
-  const float fx = (float)tg.lx, fy = (float)tg.ly;
+  // (a pixel that has stopped moves to infinity: no test passes there)
+  float fx = tg.inside ? (float)tg.lx : INFINITY;
+  const float fy = (float)tg.ly;
   const float qx = (float)(tg.lx & ~7), qy = (float)(tg.ly & ~7);
   float Tr = 1.0f;
   uint32_t cnt = 0;
-  bool alive = tg.inside;
   for (uint32_t base = rg.x; base < rg.y; base += NT) {
     const uint32_t m = min((uint32_t)NT, rg.y - base);
     __syncthreads();
@@ -392,28 +393,41 @@ __global__ __launch_bounds__(T * T) void k_render_count(const ViewDev* __restric
       }
     }
     __syncthreads();
-    uint64_t mask[NM];
-    block_masks<NM>(s0, s1, (int)m, qx, qy, mask);
-    for (int k = 0; k < NM; ++k) {
-      for (uint64_t mk = mask[k]; mk != 0ull && wave_mask(alive) != 0ull; mk &= mk - 1ull) {
-        const uint32_t j = 64u * k + (uint32_t)__builtin_ctzll(mk);
-        const float4 a0 = s0[j];
-        const float4 a1 = s1[j];
-        const float q = gauss_q(a0.z, a0.w, a1.x, a0.x - fx, a0.y - fy);
-        const bool pass = alive & passes(q, a1.y);
-        const float alpha = fminf(kAlphaMax, s2[j].x * __builtin_amdgcn_exp2f(-q));
-        const float Tn = Tr * (1.0f - alpha);
-        const bool blend = pass && !(Tn < kTMin);
-        cnt += pass ? 1u : 0u;
-        alive = alive && !(pass && Tn < kTMin);
-        Tr = blend ? Tn : Tr;
-        if (wave_mask(blend) != 0ull && __lane_id() == 0u) atomicOr(&s_eff[j >> 5], 1u << (j & 31u));
+    if (wave_mask(fx < INFINITY) != 0ull) {   // (a block whose pixels have all stopped only keeps the barriers)
+      uint64_t mask[NM];
+      block_masks<NM>(s0, s1, (int)m, qx, qy, mask);
+      for (int k = 0; k < NM; ++k) {
+        uint64_t eff = 0ull;   // this wave's blended entries of the 64, marked together
+        uint64_t mk = wave_mask(fx < INFINITY) != 0ull ? mask[k] : 0ull;
+        while (mk != 0ull) {
+          const uint32_t j = 64u * k + (uint32_t)__builtin_ctzll(mk);
+          const uint64_t bit = mk & (0ull - mk);
+          mk ^= bit;
+          const float4 a0 = s0[j];
+          const float4 a1 = s1[j];
+          const float opacity = s2[j].x;
+          const float q = gauss_q(a0.z, a0.w, a1.x, a0.x - fx, a0.y - fy);
+          const bool pass = passes(q, a1.y);
+          if (wave_mask(pass) == 0ull) continue;
+          const float alpha = fminf(kAlphaMax, opacity * __builtin_amdgcn_exp2f(-q));
+          const float Tn = Tr * (1.0f - alpha);
+          const bool stop = pass & (Tn < kTMin), blend = pass & !stop;
+          cnt += pass ? 1u : 0u;
+          Tr = blend ? Tn : Tr;
+          eff |= wave_mask(blend) != 0ull ? bit : 0ull;
+          fx = stop ? INFINITY : fx;
+          mk = wave_mask(fx < INFINITY) == 0ull ? 0ull : mk;
+        }
+        if (__lane_id() == 0u) {
+          if ((uint32_t)eff) atomicOr(&s_eff[2 * k], (uint32_t)eff);
+          if ((uint32_t)(eff >> 32)) atomicOr(&s_eff[2 * k + 1], (uint32_t)(eff >> 32));
+        }
       }
     }
     __syncthreads();
     if (threadIdx.x == 0)
       for (int w = 0; w < NT / 32; ++w) n_eff += (uint32_t)__popc(s_eff[w]);
-    if (__syncthreads_and(!alive)) break;
+    if (__syncthreads_and(!(fx < INFINITY))) break;
   }
   if (tg.inside) {
     const ViewDev& cv = views[tg.v];

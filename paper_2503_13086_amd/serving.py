@@ -283,7 +283,7 @@ class Engine:
         per pair (tile ids and record ids, ping-pong), the buffers' 25 %
         over-allocation and 320 KiB of fixed buffers (status and split counters,
         the split lists' floors, small scratch); 100 B per pixel (per-pixel forward
-        state, soft count and its gradient, SSIM statistics, image and dL/dimage)."""
+        state, soft count and its gradient, image and dL/dimage, and 36 B to spare)."""
         pairs = self.pairs_per_view if self.pairs_per_view is not None else 16 * n
         ctx = int((142 * n + 16 * pairs) * 5 // 4) + 327680
         return ctx + 100 * pixels
