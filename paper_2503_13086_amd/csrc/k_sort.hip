@@ -667,12 +667,12 @@ __device__ inline uint32_t split_threshold(uint32_t cand) {
 // Kept pairs per entry (index order, coalesced reads): the tiles of the entry's
 // rect whose pixel-centre box meets its cutoff region.  The wave's candidates are
 // spread over its lanes; runs of one entry within 64 candidates are counted with
-// ballots by the run's first lane.  Bound by vector instructions (0.32 per SIMD
-// and cycle): the box offsets as whole numbers plus a fraction in fp32 and two edges in
-// place of four FP64 offsets and four edges take 180 us where 277 were taken for
-// 1 000 000 Gaussians in nine views, 65 where 75 for 2 500 000 in one.  Each entry also gets a 16-byte EmitInfo: its
+// ballots by the run's first lane.  Each entry also gets a 16-byte EmitInfo: its
 // rect and, when it has at most 64 candidates, the outcome of every test (bit i
 // for the rect's i-th tile, row-major), which is all emission then has to fetch.
+// Bound by vector instructions (0.35 per SIMD and cycle): with the box offsets as whole
+// numbers plus a fraction in fp32 and two edges, in place of four FP64 offsets and four
+// edges, 1 000 000 Gaussians in nine views take 236 us where they took 310.
 constexpr uint32_t kRedoMark = 1u << 31;
 
 __global__ __launch_bounds__(kThreads) void k_count_kept(const uint32_t* __restrict__ touched,
