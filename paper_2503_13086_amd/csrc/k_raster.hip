@@ -117,7 +117,9 @@ __device__ inline TileGeom tile_geom(const ViewDev* __restrict__ views, int V, i
 // yields det < ulp(b^2), kappa > 1e4); kappa and kC are fp32 too (their errors only
 // move the margin by as much of itself).  A conic that is not clearly positive
 // definite (det <= 0 or kappa >= 1e4) gets t_c = inf, so every block lists it; a
-// cutoff above 0 (opacity below 1/255) gets t_c = -1, so no block does.
+// cutoff above 0 (opacity below 1/255) or NaN gets t_c = NaN, which no block's q is at
+// or below, whatever rounding made of it: the pixel test, which only sees |tau|, never
+// meets such a splat.
 //   q0 = (u', w', A, B)   q1 = (C, t, t_c, kC)   q2 = (o, r, g, b)
 // (the per-pixel test reads q0 and q1.xy, a blend q2).
 struct RawRecord {
@@ -142,7 +144,7 @@ __device__ inline void stage(const RawRecord& r, double ox, double oy, float4& q
     if (kappa < 1e4f) tc = t * (1.0f + 1e-5f * kappa);
     kc = -c.y * __builtin_amdgcn_rcpf(c.z);
   }
-  if (!(d.x <= 0.0f)) tc = -1.0f;
+  if (!(d.x <= 0.0f)) tc = NAN;
   q0 = make_float4((float)(r.uw.x - ox), (float)(r.uw.y - oy), (0.5f * c.x) * kLog2e, c.y * kLog2e);
   q1 = make_float4((0.5f * c.z) * kLog2e, t, tc, kc);
   q2 = make_float4(c.w, d.y, d.z, d.w);
@@ -152,7 +154,7 @@ __device__ inline void stage(const RawRecord& r, double ox, double oy, float4& q
 // sort): no block lists it, and no pixel would accept it.
 __device__ inline void stage_empty(float4& q0, float4& q1, float4& q2) {
   q0 = make_float4(NAN, 0.f, 0.f, 0.f);
-  q1 = make_float4(0.f, 0.f, -1.f, 0.f);
+  q1 = make_float4(0.f, 0.f, NAN, 0.f);
   q2 = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
