@@ -487,6 +487,15 @@ constexpr int kPanel = 8;
 constexpr int kGroup = 4;
 typedef __attribute__((address_space(3))) double LdsDouble;
 
+// A pixel that did not blend a candidate enters its sums as alpha = 0 times finite
+// numbers, which takes no select.  The numbers are finite while upstream gradients are
+// below kTame: their product with a colour below it, summed with weights
+// of at most 1 in all and divided by 1 - alpha >= 0.01, stays under 1e33.  A wavefront
+// with anything larger, infinite or NaN drops the candidates that none of its pixels
+// blends and sets the derivative of the pixels that did not blend one to zero: such a
+// value then reaches no splat but those blended with it.
+constexpr float kTame = 1e15f;
+
 // Panel position of pixel pair (row, u): pixels 2 u and 2 u + 1 of a row form a
 // 16-byte unit, and the units of a row are permuted by xor with unit_turn.  The 16
 // lanes (two slots, eight rows) that one LDS cycle serves then read 16 different
@@ -592,6 +601,8 @@ __global__ __launch_bounds__(T * T) __attribute__((amdgpu_waves_per_eu(4))) void
     if (rid < n_rec) raw = fetch(rec, rid);
   };
   fetch_batch(jmax);
+  const bool wild_pixel = wave_mask(!(fabsf(g0) + fabsf(g1) + fabsf(g2) + fabsf(gG) <= kTame &&
+                                      fabsf(Sg) <= kTame * kTame)) != 0ull;
   for (int end = jmax; end > 0; end -= NB) {
     const int beg = end > NB ? end - NB : 0;
     const int m = end - beg;
@@ -624,16 +635,30 @@ __global__ __launch_bounds__(T * T) __attribute__((amdgpu_waves_per_eu(4))) void
       }
       cnt += hits;
     }
-    const bool caps = wave_mask(opaque) != 0ull;   // some candidate's alpha may reach the cap
+    const bool wild = wild_pixel;
+    const bool caps = wave_mask(opaque) != 0ull || wild;   // some candidate's alpha may reach the cap
+    const uint32_t lrel16 = 16u * lrel;
+    if (wild) {
+      // candidates that no pixel of the block blends leave the list (see kTame)
+      __builtin_amdgcn_wave_barrier();
+      int kept = 0;
+      for (int c = 0; c < cnt; ++c) {
+        const uint32_t off = list[wave][c];
+        const float4 a0 = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(s0) + off);
+        const float2 a1 = *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(s1) + off);
+        const float q = gauss_q(a0.z, a0.w, a1.x, a0.x - fx, a0.y - fy);
+        if (wave_mask((off < lrel16) & passes(q, a1.y)) != 0ull) list[wave][kept++] = off;
+      }
+      cnt = kept;
+    }
     if (lane < kPanel) list[wave][cnt + lane] = 16u * NB;
     __builtin_amdgcn_wave_barrier();
-    const uint32_t lrel16 = 16u * lrel;
     // candidates base + h .. base + h + G - 1: their tests and alphas do not depend on
     // each other, so G of them hide each other's latency where few waves are resident
     const auto group = [&](auto cap, int first, int h) {
       constexpr bool CAP = decltype(cap)::value;
         float alpha[G], ri[G], cg[G];
-        bool capped[G];
+        bool none[G];   // no derivative: a capped alpha, or a pixel that did not blend (see kTame)
 #pragma unroll
         for (int g = 0; g < G; ++g) {
           const uint32_t off = list[wave][first + g];
@@ -647,8 +672,9 @@ __global__ __launch_bounds__(T * T) __attribute__((amdgpu_waves_per_eu(4))) void
           // exactly, transmittance and weight need no select and every sum gets zeros
           alpha[g] = on ? og : 0.0f;
           if (CAP) {
-            capped[g] = alpha[g] > kAlphaMax;
-            alpha[g] = capped[g] ? kAlphaMax : alpha[g];
+            none[g] = alpha[g] > kAlphaMax;
+            alpha[g] = none[g] ? kAlphaMax : alpha[g];
+            none[g] |= !on;
           }
           ri[g] = __builtin_amdgcn_rcpf(1.0f - alpha[g]);
           cg[g] = __fmaf_rn(g2, a2.w, __fmaf_rn(g1, a2.z, g0 * a2.y));
@@ -663,7 +689,7 @@ __global__ __launch_bounds__(T * T) __attribute__((amdgpu_waves_per_eu(4))) void
           const float dLda = __fmaf_rn(Tr, cg[g], __fmaf_rn(-Sg, ri[g], gG));
           Sg = __fmaf_rn(cg[g], wgt, Sg);
           float dpow = dLda * alpha[g];
-          if (CAP) dpow = capped[g] ? 0.0f : dpow;
+          if (CAP) dpow = none[g] ? 0.0f : dpow;
           pan[(h + g) & 1][64 * (h + g)] = make_float2(dpow, wgt);
         }
     };
