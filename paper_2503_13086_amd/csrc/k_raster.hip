@@ -196,6 +196,17 @@ __device__ inline void block_masks(const float4* s0, const float4* s1, int m, fl
   }
 }
 
+// A pixel that did not blend a candidate enters every sum as alpha = 0 times finite
+// numbers, which takes no select.  The numbers are finite while colours and upstream
+// gradients are below kTame: their product, summed with weights of at most 1 in all and
+// divided by 1 - alpha >= 0.01, stays under 1e33.  A wavefront with anything larger,
+// infinite or NaN leaves out the candidates that none of its pixels blends, and in the
+// backward sets the derivative of the pixels that did not blend one to zero: such a
+// value then reaches no splat but those blended with it, and no block but those that
+// blend it.
+constexpr float kTame = 1e15f;
+__device__ inline bool tame_colour(const float4& q2) { return fabsf(q2.y) + fabsf(q2.z) + fabsf(q2.w) <= kTame; }
+
 // x << 1, with the lane's bit of a wave-wide mask shifted in (one add with carry).
 __device__ inline uint32_t shift_in(uint32_t x, uint64_t m) {
   uint32_t r;
@@ -264,6 +275,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k
     const bool hit = rid < n_rec && block_hit(q0, q1, qx, qy);
     const uint64_t mk = wave_mask(hit);
     const bool caps = wave_mask(hit && q2.x > kAlphaMax) != 0ull;   // some alpha may reach the cap
+    const bool wild = wave_mask(hit && !tame_colour(q2)) != 0ull;
     const int n = __popcll(mk);
     __builtin_amdgcn_wave_barrier();
     if (hit) {
@@ -284,8 +296,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k
     // pass, stop or still blend live in scalar registers.  `hist` collects one bit per
     // candidate and pixel (blended or not), which gives the count and the last
     // position once per 32 candidates.
-    const auto walk = [&](auto cap) {
-      constexpr bool CAP = decltype(cap)::value;
+    const auto walk = [&](auto cap, auto wild_colours) {
+      constexpr bool CAP = decltype(cap)::value, WILD = decltype(wild_colours)::value;
       for (int i0 = 0; i0 < n && live != 0ull; i0 += 32) {
         uint32_t hist = 0u;
         int i = i0;
@@ -309,6 +321,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k
 #pragma unroll
           for (int g = 0; g < G; ++g) {
             uint64_t m = pass[g] & live;
+            if (WILD && m == 0ull) {   // (its colour times 0 would be NaN)
+              hist = shift_in(hist, 0ull);
+              continue;
+            }
             float alpha = __builtin_amdgcn_inverse_ballot_w64(m) ? al[g] : 0.0f;   // 0 where it does not blend
             float Tn = Tr * (1.0f - alpha);
             const uint64_t stops = wave_mask(Tn < kTMin);
@@ -333,8 +349,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k
         if (hist != 0u) lastp = __float_as_uint(r0[ROWS + i - __ffs((int)hist)].z);
       }
     };
-    if (caps) walk(std::true_type{});
-    else walk(std::false_type{});
+    if (wild) walk(std::true_type{}, std::true_type{});
+    else if (caps) walk(std::true_type{}, std::false_type{});
+    else walk(std::false_type{}, std::false_type{});
     raw = raw1;
     rid = rid1;
     rid1 = rid2;
@@ -487,15 +504,6 @@ constexpr int kPanel = 8;
 constexpr int kGroup = 4;
 typedef __attribute__((address_space(3))) double LdsDouble;
 
-// A pixel that did not blend a candidate enters its sums as alpha = 0 times finite
-// numbers, which takes no select.  The numbers are finite while upstream gradients are
-// below kTame: their product with a colour below it, summed with weights
-// of at most 1 in all and divided by 1 - alpha >= 0.01, stays under 1e33.  A wavefront
-// with anything larger, infinite or NaN drops the candidates that none of its pixels
-// blends and sets the derivative of the pixels that did not blend one to zero: such a
-// value then reaches no splat but those blended with it.
-constexpr float kTame = 1e15f;
-
 // Panel position of pixel pair (row, u): pixels 2 u and 2 u + 1 of a row form a
 // 16-byte unit, and the units of a row are permuted by xor with unit_turn.  The 16
 // lanes (two slots, eight rows) that one LDS cycle serves then read 16 different
@@ -623,7 +631,7 @@ __global__ __launch_bounds__(T * T) __attribute__((amdgpu_waves_per_eu(4))) void
     block_masks<NM>(s0, s1, min(m, wave_last - beg), qx, qy, mask);
     const uint32_t lrel = lp > (uint32_t)beg ? lp - (uint32_t)beg : 0u;   // batch positions this pixel blended
     int cnt = 0;
-    bool opaque = false;
+    bool opaque = false, wild_colour = false;
 #pragma unroll
     for (int k = NM - 1; k >= 0; --k) {
       const uint64_t mk = mask[k];
@@ -631,11 +639,13 @@ __global__ __launch_bounds__(T * T) __attribute__((amdgpu_waves_per_eu(4))) void
       if ((mk >> lane) & 1ull) {
         // its rank from the back
         list[wave][cnt + hits - 1 - mask_rank(mk)] = 16u * (uint32_t)(64 * k + lane);
-        opaque |= s2[64 * k + lane].x > kAlphaMax;
+        const float4 a2 = s2[64 * k + lane];
+        opaque |= a2.x > kAlphaMax;
+        wild_colour |= !tame_colour(a2);
       }
       cnt += hits;
     }
-    const bool wild = wild_pixel;
+    const bool wild = wild_pixel || wave_mask(wild_colour) != 0ull;
     const bool caps = wave_mask(opaque) != 0ull || wild;   // some candidate's alpha may reach the cap
     const uint32_t lrel16 = 16u * lrel;
     if (wild) {

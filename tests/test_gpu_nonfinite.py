@@ -2,8 +2,10 @@
 
 Of an upstream gradient at one pixel only the splats which that pixel blended get a
 non-finite centre, conic or opacity gradient, and only splats that blend into some pixel
-of its 8x8 block a non-finite colour gradient.  Everything else is the same bits as
-without the value (in the fixed summation order)."""
+of its 8x8 block a non-finite colour gradient; a splat of infinite colour that no pixel of
+a block takes (between the pixel centres, of barely more than the cutoff opacity) leaves
+the block's image, and every other splat's gradient, as they are.  Everything else is the
+same bits as without the value (in the fixed summation order)."""
 import numpy as np
 import pytest
 
@@ -62,3 +64,32 @@ def test_upstream_gradient_of_one_pixel(tile, value, opaque):
     assert np.array_equal(a[not_here, :6], b[not_here, :6])
     assert np.array_equal(a[not_block], b[not_block])
     assert not np.isfinite(dirty["grad2d"].reshape(sc.n, 9)[~not_here]).all()
+
+
+@pytest.mark.parametrize("opaque", [False, True])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("tile", [8, 16, 32])
+def test_colour_of_a_splat_that_no_pixel_takes(tile, value, opaque):
+    sc = _scene(opaque=opaque)
+    rng = np.random.default_rng(9)
+    k = 40
+    P = sc.params
+    P[0, :k] = (rng.integers(1, W, k) - W / 2) / 16            # between pixel centres
+    P[1, :k] = (rng.integers(1, H, k) - H / 2) / 16
+    P[2, :k] = rng.choice([-1.0, 1.0], k) * 1e-3
+    P[0, :k] *= (4 + P[2, :k]) / 4
+    P[1, :k] *= (4 + P[2, :k]) / 4
+    P[3:6, :k] = -9.0                                          # the cutoff region: 0.1 pixels across
+    o = 1.005 / 255
+    P[10, :k] = np.log(o / (1 - o))
+    up = scenegen.upstream_grads(3, sc.cams, 1e-2)
+    clean = gu.run_gpu(sc, upstream=up, tile=tile, bwd="ordered")
+    P[11:14, :k] = value
+    dirty = gu.run_gpu(sc, upstream=up, tile=tile, bwd="ordered")
+    off = _exponents(clean)
+    assert off[:k].all() and not off[k:].all()
+    assert dirty["K"] == clean["K"] and (clean["values"] < k).sum() >= k // 2
+    assert np.array_equal(clean["color"][0].view(np.uint32), dirty["color"][0].view(np.uint32))
+    for key in ("n_contrib", "last", "evals"):
+        assert np.array_equal(clean[key], dirty[key]), key
+    assert np.array_equal(clean["grad2d"].view(np.uint32), dirty["grad2d"].view(np.uint32))
