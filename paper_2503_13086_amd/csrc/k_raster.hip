@@ -766,10 +766,12 @@ __global__ __launch_bounds__(T * T) __attribute__((amdgpu_waves_per_eu(4))) void
     if ((int)threadIdx.x < m) {
       Acc* ar = acc[0][threadIdx.x];
       float a[kGrad2D];
-      for (int c = 0; c < kGrad2D; ++c) {
-        a[c] = (float)ar[c];
-        for (int w = 1; w < NACC; ++w) a[c] += (float)acc[w][threadIdx.x][c];
-      }
+      for (int c = 0; c < kGrad2D; ++c) a[c] = (float)ar[c];
+      // (two waves' rows in flight at T = 32: with all sixteen, 71 registers went to scratch memory)
+      constexpr int kRowsAhead = NACC > 4 ? 2 : 4;
+#pragma unroll kRowsAhead
+      for (int w = 1; w < NACC; ++w)
+        for (int c = 0; c < kGrad2D; ++c) a[c] += (float)acc[w][threadIdx.x][c];
       // moments -> partials: with exponent p = -(a dx^2 + 2 b dx dy + c dy^2)/2 and the
       // staged coefficients A, B, C = (a/2, b, c/2) log2(e):
       // dp/du = -ln2 (2A dx + B dy), dp/dw = -ln2 (B dx + 2C dy),
