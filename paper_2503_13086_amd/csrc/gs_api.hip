@@ -23,12 +23,11 @@ struct DevBuf {
 
 enum Stage { kNone = 0, kProjected = 1, kBinned = 2, kRendered = 3 };
 
-// Scratch of gs_loss_noalloc: the per-tile loss sums (two doubles per 32x32 loss
-// tile), 1 MiB that every GPU the library runs on holds until the process ends.
+// Scratch of gs_loss_noalloc: the loss sums of its largest views, 9 MiB that every GPU
+// the library runs on holds until the process ends.
 // In host code this name is a host-side stand-in, not a device address: host code
 // uses the per-device address gs_create looks up (scratch_ptr).
-constexpr size_t kNoAllocLossTiles = 65536;
-static __device__ __align__(256) double scratch[2 * kNoAllocLossTiles];
+static __device__ __align__(256) double scratch[2 * kLossSums];
 
 constexpr int kMaxScratchDevices = 256;
 std::mutex scratch_mu;
@@ -665,7 +664,8 @@ gs_status gs_loss(gs_ctx* c, const float* color, const float* target, float w_l1
   hipStream_t s = (hipStream_t)stream;
   GS_HIP(c, hipSetDevice(c->device));
   gs_status st;
-  if ((st = ensure(c, c->lossp, (size_t)loss_partials(c->hviews.data(), c->V) * 16, s)) != GS_OK) return st;
+  const LossPlan plan = loss_plan(c->hviews.data(), c->V, w_dssim != 0.0f);
+  if ((st = ensure(c, c->lossp, (size_t)plan.sums.off[c->V] * 16, s)) != GS_OK) return st;
   // a gradient written over one of the images goes through a buffer: the SSIM term
   // reads both around every pixel
   const size_t image = (size_t)c->P * 3 * 4;
@@ -676,8 +676,8 @@ gs_status gs_loss(gs_ctx* c, const float* color, const float* target, float w_l1
   const bool via = w_dssim != 0.0f && (over(color) || over(target));
   if (via && (st = ensure(c, c->aux, image, s)) != GS_OK) return st;
   Prof pr(c, GS_K_LOSS, s);
-  GS_HIP(c, launch_loss_dev(c->views.as<ViewDev>(), c->hviews.data(), c->V, color, target, w_l1, w_dssim,
-                            c->lossp.as<double>(), loss_out, via ? c->aux.as<float>() : dL_dcolor, s));
+  GS_HIP(c, launch_loss_dev(c->views.as<ViewDev>(), c->V, plan, color, target, w_l1, w_dssim, c->lossp.as<double>(),
+                            loss_out, via ? c->aux.as<float>() : dL_dcolor, s));
   if (via) GS_HIP(c, hipMemcpyAsync(dL_dcolor, c->aux.as<float>(), image, hipMemcpyDeviceToDevice, s));
   return GS_OK;
 }
@@ -692,17 +692,18 @@ gs_status gs_loss_noalloc(gs_ctx* c, const float* color, const float* target, fl
   if (loss_out && !aligned(loss_out, 8)) return fail(c, GS_ERR_INVALID, "loss_out misaligned");
   if (!std::isfinite(w_l1) || !std::isfinite(w_dssim)) return fail(c, GS_ERR_INVALID, "non-finite loss weight");
   const size_t tiles = (size_t)loss_tiles(c->hviews.data(), c->V);
-  if (tiles > kNoAllocLossTiles) {
+  if (tiles > kLossTiles) {
     char buf[160];
     std::snprintf(buf, sizeof buf, "gs_loss_noalloc: the views hold %zu 32x32 loss tiles, more than its %zu",
-                  tiles, kNoAllocLossTiles);
+                  tiles, kLossTiles);
     return fail(c, GS_ERR_CAPACITY, buf);
   }
   void* sp = scratch_for(c->device);
   if (!sp) return fail(c, GS_ERR_UNSUPPORTED, "gs_loss_noalloc: no scratch address for this device");
   GS_HIP(c, hipSetDevice(c->device));
-  // every tile's sums are written before they are read: nothing to clear
-  GS_HIP(c, launch_loss_dev(c->views.as<ViewDev>(), c->hviews.data(), c->V, color, target, w_l1, w_dssim,
+  // every sum is written before it is read: nothing to clear
+  const LossPlan plan = loss_plan(c->hviews.data(), c->V, w_dssim != 0.0f);
+  GS_HIP(c, launch_loss_dev(c->views.as<ViewDev>(), c->V, plan, color, target, w_l1, w_dssim,
                             reinterpret_cast<double*>(sp), loss_out, dL_dcolor, (hipStream_t)stream));
   return GS_OK;
 }

@@ -345,18 +345,30 @@ hipError_t launch_ordered_sum(const uint32_t* pair_rec, size_t K_cap, const unsi
                               uint32_t* keys_b, uint32_t* vals_b, uint2* eranges, SortScratch scratch,
                               float* grad2d, hipStream_t s);
 
-// Loss over all views.  partials: 2 doubles for each of loss_partials() tiles, which are
-// at most loss_tiles() (the views' 32x32 tiles) where those are more than 8192.
-// dL_dcolor must not overlap the images when w_dssim != 0 (neighbouring tiles read
-// them after this one's gradient is written).
+// Loss over all views, cut into 32x32 tiles (L1 alone) or strips of 44 columns by some
+// blocks of rows (with the SSIM term); each tile, or each block of a channel's strip,
+// leaves its L1 and SSIM sums.
+struct LossOffsets {
+  int32_t off[GS_MAX_VIEWS + 1];   // first of each view, and the end of the last
+};
+struct LossPlan {
+  LossOffsets tiles, sums;          // tiles (a strip of all three channels) and pairs of sums
+  uint8_t block[GS_MAX_VIEWS];      // SSIM: rows of a view's blocks, in windows of 11
+  uint8_t blocks[GS_MAX_VIEWS];     // and blocks of its strips
+};
+LossPlan loss_plan(const ViewDev* hviews, int V, bool ssim);
+// Views of at most kLossTiles 32x32 tiles (loss_tiles) have at most kLossSums pairs of sums.
 int loss_tiles(const ViewDev* hviews, int V);
-int loss_partials(const ViewDev* hviews, int V);
+constexpr size_t kLossTiles = 65536;
+constexpr size_t kLossSums = 9 * kLossTiles;
 // Eq. 9 on the soft count asum [P]: per-view loss w std (loss_out, may be NULL)
 // and dL/dG [P]; partials: V x load_chunks doubles2, stats: V doubles2
 int load_chunks(const ViewDev* hviews, int V);
 hipError_t launch_load_balance(const ViewDev* dviews, const ViewDev* hviews, int V, const float* asum, float w,
                                double* partials, double* stats, double* loss_out, float* dG, hipStream_t s);
-hipError_t launch_loss_dev(const ViewDev* dviews, const ViewDev* hviews, int V, const float* color,
+// partials: plan.sums.off[V] pairs of doubles.  dL_dcolor must not overlap the images when
+// w_dssim != 0 (neighbouring strips read them after this one's gradient is written).
+hipError_t launch_loss_dev(const ViewDev* dviews, int V, const LossPlan& plan, const float* color,
                            const float* target, float w_l1, float w_dssim, double* partials, double* loss_out,
                            float* dL_dcolor, hipStream_t s);
 

@@ -14,7 +14,8 @@
 // and dS_mean/dx = (window * A + 2 x (window * B) + y (window * Cc)) / N (the window
 // is symmetric), with 1/D1 and 1/D2 taken once per pixel from the hardware reciprocal.
 // k_ssim forms all of it in one pass over the images.
-// Loss sums are reduced per workgroup in FP64.
+// Loss sums are taken in FP64, over blocks of a view that its own size decides and then
+// over the view's blocks in order: a view's loss is the same bits in any batch.
 //
 // The load-balancing term of Eq. 9 (kernels at the end) works on the soft
 // per-pixel Gaussian count the forward writes.
@@ -26,8 +27,9 @@ namespace {
 constexpr int LT = 32;              // k_l1's tile edge
 constexpr int R = 5;                // window radius
 constexpr int TAPS = 2 * R + 1;
-constexpr int kSsimOccupancy = 3;   // k_ssim's wavefronts per SIMD (147 registers; at four they spill)
+constexpr int kSsimOccupancy = 3;   // k_ssim's wavefronts per SIMD (156 registers; at four they spill)
 constexpr int SW = 64 - 4 * R;      // k_ssim: output columns of a wavefront (two windows less than its lanes)
+constexpr int kMaxRows = 12;        // k_ssim's strips: at most so many TAPS rows
 constexpr float kC1 = 0.01f * 0.01f;
 constexpr float kC2 = 0.03f * 0.03f;
 
@@ -35,11 +37,6 @@ struct Win {
   float w[TAPS];
 };
 
-// global offset of each view's tiles (n_views + 1 entries): 32x32 pixels (k_l1) or SW
-// columns by a number of rows (k_ssim)
-struct LossTiles {
-  int32_t off[GS_MAX_VIEWS + 1];
-};
 
 __device__ inline double block_sum_d(double x, double* sh) {
   for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
@@ -66,22 +63,26 @@ __host__ __device__ inline int xcd_tile_chunk(int n_tiles) { return (n_tiles + k
 
 __device__ inline int xcd_tile(int b, int n_tiles) { return (b % kXcds) * xcd_tile_chunk(n_tiles) + b / kXcds; }
 
-__device__ inline TileLoc loss_tile(const ViewDev* __restrict__ views, const LossTiles& lt, int V, int tile, int tw,
-                                    int th) {
+__device__ inline int loss_view(const LossOffsets& lt, int V, int tile) {
   int v = 0;
   while (v + 1 < V && tile >= lt.off[v + 1]) ++v;
-  const int nx = (views[v].W + tw - 1) / tw;
-  const int local = tile - lt.off[v];
-  return TileLoc{v, (local % nx) * tw, (local / nx) * th};
+  return v;
 }
 
-__global__ __launch_bounds__(256) void k_l1(const ViewDev* __restrict__ views, int V, LossTiles lt,
+__device__ inline TileLoc loss_tile(const ViewDev* __restrict__ views, const LossOffsets& lt, int V, int tile) {
+  const int v = loss_view(lt, V, tile);
+  const int nx = (views[v].W + LT - 1) / LT;
+  const int local = tile - lt.off[v];
+  return TileLoc{v, (local % nx) * LT, (local / nx) * LT};
+}
+
+__global__ __launch_bounds__(256) void k_l1(const ViewDev* __restrict__ views, int V, LossOffsets lt,
                                              const float* __restrict__ x, const float* __restrict__ y, float w_l1,
                                              float* __restrict__ grad, double2* __restrict__ partials) {
   __shared__ double sh[4];
   const int tile = xcd_tile(blockIdx.x, lt.off[V]);
   if (tile >= lt.off[V]) return;
-  const TileLoc t = loss_tile(views, lt, V, tile, LT, LT);
+  const TileLoc t = loss_tile(views, lt, V, tile);
   const ViewDev& cv = views[t.v];
   const size_t hw = (size_t)cv.W * cv.H;
   const size_t base = 3 * (size_t)cv.pix_off;
@@ -163,35 +164,77 @@ __device__ inline void window_cols_sum(const float (&w)[R + 1], const Neighbours
   for (int q = 0; q < Q; ++q) asm volatile("" : "+v"(out[q]));
 }
 
+// Sums over the wavefront, a's in the lower 32 lanes and b's in the upper: half_sums pairs
+// the lanes, whole_sums finishes.  By lane swaps and DPP (shuffles through LDS would hold
+// a register for every lane distance).
+struct Words {
+  uint32_t lo, hi;
+};
+__device__ inline Words words(double x) {
+  const uint64_t u = (uint64_t)__double_as_longlong(x);
+  return Words{(uint32_t)u, (uint32_t)(u >> 32)};
+}
+__device__ inline double from_words(uint32_t lo, uint32_t hi) {
+  return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+template <int CTRL>
+__device__ inline double dpp_add(double x) {
+  const Words w = words(x);
+  return x + from_words((uint32_t)__builtin_amdgcn_update_dpp(0, (int)w.lo, CTRL, 0xf, 0xf, true),
+                        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w.hi, CTRL, 0xf, 0xf, true));
+}
+__device__ inline double half_sums(double a, double b) {
+  const Words wa = words(a), wb = words(b);
+  const auto l32 = __builtin_amdgcn_permlane32_swap(wa.lo, wb.lo, false, false);
+  const auto h32 = __builtin_amdgcn_permlane32_swap(wa.hi, wb.hi, false, false);
+  return from_words(l32[0], h32[0]) + from_words(l32[1], h32[1]);
+}
+__device__ inline double whole_sums(double x) {
+  const Words w = words(x);
+  const auto l16 = __builtin_amdgcn_permlane16_swap(w.lo, w.lo, false, false);
+  const auto h16 = __builtin_amdgcn_permlane16_swap(w.hi, w.hi, false, false);
+  x = from_words(l16[0], h16[0]) + from_words(l16[1], h16[1]);
+  x = dpp_add<0x128>(x);    // lane l ^ 8
+  x = dpp_add<0x141>(x);    // lane 7 - l of its eight
+  x = dpp_add<0x4E>(x);     // lane l ^ 2
+  return dpp_add<0xB1>(x);  // lane l ^ 1
+}
+
 // The SSIM term and both terms' gradient.  A wavefront takes one channel of SW columns
-// by `rows` rows and walks down them, a lane per column: each row's four maps go through
-// LDS into the horizontal windows and from there into the vertical ones; the row these
-// finish gives S and A, B, Cc, which go through the second horizontal and vertical
-// windows, and the row those finish is a row of the gradient.  So each image is read once (and a fifth around it), nothing else but
-// the gradient touches HBM and no barrier is met.  What it does again: a tile passes
-// over rows + 4R rows and 64 columns for its SW.
+// by some rows (a strip) and walks down them, a lane per column: each row's four maps go
+// through LDS into the horizontal windows and from there into the vertical ones; the row
+// these finish gives S and A, B, Cc, which go through the second horizontal and vertical
+// windows, and the row those finish is a row of the gradient.  So each image is read once
+// (and a fifth around it), nothing else but the gradient touches HBM and no barrier is
+// met.  What it does again: a strip passes over its rows + 4R rows and 64 columns for its
+// SW.
+// The sums of each block of a strip (some TAPS rows, see ssim_block) are kept by
+// themselves, so that they do not depend on how many blocks a strip has: in LDS, folded
+// over the lanes at the end (in the loop that takes 10 registers, and 10 % more time for
+// the spills).
 // Bound by instruction issue (about 185 vector instructions a row, of which 154 the
 // windows' multiply-adds) and the 22 16-byte LDS accesses a row beside it.  It replaced
 // two kernels over 32x32 tiles with the statistics in HBM between them (36 bytes a pixel
 // written and read) and, for gs_loss_noalloc, one over 52x52 patches: 10.1 Mpix in 9
-// views 431 -> 290 us (both terms and the final sums), 1600x1067 91 -> 76, 1296x864
-// 71 -> 56, three views of 0.2 Mpix in all 45 -> 27.
-template <int WAVES>
-__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kSsimOccupancy))) void k_ssim(
-    const ViewDev* __restrict__ views, int V, LossTiles lt, int rows, const float* __restrict__ x,
+// views 427 -> 299 us (both terms and the final sums), 1600x1067 88 -> 74, 1296x864
+// 63 -> 53, three views of 0.2 Mpix in all 38 -> 23.
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kSsimOccupancy))) void k_ssim(
+    const ViewDev* __restrict__ views, int V, LossPlan plan, const float* __restrict__ x,
     const float* __restrict__ y, Win win, float w_l1, float w_dssim, float* __restrict__ grad,
-    double2* __restrict__ partials) {
-  static_assert(WAVES == 1 || WAVES == 3, "a channel or all three");
-  __shared__ float4 bufs[WAVES][2][64 + TAPS - 1];
-  __shared__ double2 sums[3];
-  const int part = xcd_tile(blockIdx.x, WAVES == 1 ? 3 * lt.off[V] : lt.off[V]);
-  const int tile = WAVES == 1 ? part / 3 : part;
-  if (tile >= lt.off[V]) return;
-  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64), ch = WAVES == 1 ? part % 3 : wave;
-  float4 (*buf)[64 + TAPS - 1] = bufs[wave];
-  const TileLoc t = loss_tile(views, lt, V, tile, SW, rows);
-  const ViewDev& cv = views[t.v];
+    double* __restrict__ partials) {
+  __shared__ float4 buf[2][64 + TAPS - 1];
+  __shared__ double lane_sums[kMaxRows][64];
+  const int wave = xcd_tile(blockIdx.x, 3 * plan.tiles.off[V]), tile = wave / 3, ch = wave % 3;
+  if (tile >= plan.tiles.off[V]) return;
+  const int v = loss_view(plan.tiles, V, tile);
+  const ViewDev& cv = views[v];
   const int W = cv.W, H = cv.H, lane = __lane_id();
+  const int cols = (W + SW - 1) / SW, local = tile - plan.tiles.off[v], block = plan.block[v];
+  const int rows = TAPS * block * plan.blocks[v], nb = (H + TAPS * block - 1) / (TAPS * block);
+  const TileLoc t{v, (local % cols) * SW, (local / cols) * rows};
+  // the strip's sums: its blocks' pairs, after those of the channels and strips before it
+  double* sums = partials + 2 * ((size_t)plan.sums.off[v] + (size_t)((ch * cols + local % cols) * nb) +
+                                 (size_t)((local / cols) * plan.blocks[v]));
   const size_t hw = (size_t)W * H;
   const size_t plane = 3 * (size_t)cv.pix_off + ch * hw;
   const float invN = 1.0f / (float)(3 * hw);
@@ -206,8 +249,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kSsi
   const int cin = t.x0 - 2 * R + lane, cst = cin + R, cout = t.x0 + lane;
   const bool st_ok = cst >= 0 && cst < W, out_ok = lane < SW && cout < W;
   const bool st_own = st_ok && lane >= R && lane < SW + R;   // counted here
-  const int y_end = min(t.y0 + rows, H);                     // rows of this tile: [y0, y_end)
-  const int n_in = y_end - t.y0 + 4 * R;                     // input rows y0 - 2R ..
+  const int y_end = min(t.y0 + rows, H);                     // rows of this strip: [y0, y_end)
   // The images go through buffer descriptors that begin at the first row read (or the
   // tile's own first row) and end with the image: what lies outside reads as zero, the
   // padding, and is not written, with no branch around a load or a store (at which all
@@ -237,7 +279,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kSsi
 #pragma unroll
     for (int q = 0; q < 3; ++q) acc2[q][j] = 0.0f;
   }
-  double sl1 = 0.0, sss = 0.0;
+  double sl1 = 0.0, sss = 0.0, sss_block = 0.0;
+  bool ends = false;   // this block's last rows are on their way
   // image values of the next AHEAD rows
   constexpr int AHEAD = 2;
   float nx[AHEAD], ny[AHEAD];
@@ -296,6 +339,11 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kSsi
     const bool ok = st_ok && rst >= 0 && rst < H, own = st_own && rst >= t.y0 && rst < y_end;
     const float abc[3] = {ok ? __fmaf_rn(2.0f * my * (N2 - N1), rden, 2.0f * mx * S * (r2 - r1)) : 0.0f,
                           ok ? -S * r2 : 0.0f, ok ? 2.0f * N1 * rden : 0.0f};
+    // (at u = 3R mod TAPS the statistics enter the next TAPS rows)
+    if (u == 3 * R % TAPS) {
+      sss_block = sss;
+      sss = ends ? 0.0 : sss;
+    }
     sss += own ? (double)S : 0.0;
     window_cols_sum<4>(w, nb1, h1);
     Neighbours<3> nb2;
@@ -311,35 +359,36 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kSsi
     window_cols_sum<4>(w, nb1, h1);
     window_rows<4>(u, w, h1, acc1, m);
   }
-  for (int i = 2 * R; i < n_in; i += TAPS)   // (rows past n_in, in the last tile of a column, are all outside)
+  // After k rounds of TAPS rows the gradient has its first TAPS (k - 1) rows and the
+  // statistics are R + 1 rows ahead.
+  const int rounds = (y_end - t.y0 + TAPS - 1) / TAPS;
+  int left = block + 1, done = 0;
+  for (int k = 0; k <= rounds; ++k) {   // (rows past y_end, at the bottom of a view, are all outside)
+    ends = --left == 0 || k == rounds;
 #pragma unroll
-    for (int u = 0; u < TAPS; ++u) row((2 * R + u) % TAPS, i + u);
-  window_rows<3>((2 * R + TAPS - 1) % TAPS, w, h2, acc2, g);
-  give(g);
-  for (int o = 32; o > 0; o >>= 1) {
-    sl1 += __shfl_xor(sl1, o);
-    sss += __shfl_xor(sss, o);
+    for (int u = 0; u < TAPS; ++u) row((2 * R + u) % TAPS, 2 * R + TAPS * k + u);
+    lane_sums[done][lane] = half_sums(sl1, sss_block);   // (whole after the block's last round)
+    sl1 = ends ? 0.0 : sl1;
+    done += ends ? 1 : 0;
+    left = ends ? block : left;
   }
-  if (WAVES == 1) {
-    if (lane == 0) partials[part] = make_double2(sl1, sss);
-    return;
+  for (int b = 0; b < done; ++b) {
+    const double sum = whole_sums(lane_sums[b][lane]);
+    if ((lane & 31) == 0) sums[2 * b + (lane >> 5)] = sum;
   }
-  if (lane == 0) sums[ch] = make_double2(sl1, sss);
-  __syncthreads();
-  if (threadIdx.x == 0)
-    partials[tile] = make_double2(sums[0].x + sums[1].x + sums[2].x, sums[0].y + sums[1].y + sums[2].y);
 }
 
-// One workgroup per view: the view's tile partials summed in FP64.
-__global__ __launch_bounds__(256) void k_loss_final(const ViewDev* __restrict__ views, LossTiles lt,
-                                                     const double2* __restrict__ partials, int per_tile,
-                                                     float w_l1, float w_dssim, int ssim,
-                                                     double* __restrict__ out) {
-  __shared__ double sh[4];
+// One workgroup per view: the view's partial sums added up in FP64.
+constexpr int kFinalThreads = 256;
+__global__ __launch_bounds__(kFinalThreads) void k_loss_final(const ViewDev* __restrict__ views, LossOffsets lt,
+                                                              const double2* __restrict__ partials, float w_l1,
+                                                              float w_dssim, int ssim, double* __restrict__ out) {
+  __shared__ double sh[kFinalThreads / 64];
   const int v = blockIdx.x;
   const ViewDev& cv = views[v];
   double a = 0.0, b = 0.0;
-  for (int t = per_tile * lt.off[v] + threadIdx.x; t < per_tile * lt.off[v + 1]; t += blockDim.x) {
+#pragma unroll 4
+  for (int t = lt.off[v] + threadIdx.x; t < lt.off[v + 1]; t += kFinalThreads) {
     const double2 pt = partials[t];
     a += pt.x;
     b += pt.y;
@@ -447,50 +496,75 @@ int loss_tiles(const ViewDev* hviews, int V) {
 }
 
 namespace {
-constexpr int kSsimParts = 65536;   // partial sums that always fit (gs_loss_noalloc's array)
-constexpr int kSsimWaves = 1024 * kSsimOccupancy;   // wavefronts the chip holds at once
+constexpr int kSimds = 1024;
 
-int64_t ssim_tiles(const ViewDev* hviews, int V, int rows) {
-  int64_t t = 0;
-  for (int v = 0; v < V; ++v)
-    t += (int64_t)((hviews[v].W + SW - 1) / SW) * ((hviews[v].H + rows - 1) / rows);
-  return t;
+int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+// A strip of r rows passes over r + 4R, so taller is less work, but all its rows one after
+// the other.  A row takes 0.6 us with one wavefront to a SIMD, 0.7 with two and 1.0 with
+// the three that fit, so what a launch takes goes with its rows times that, summed over
+// the rounds.  Measured: 1600x1067 77 us with 33 rows (3663 wavefronts), 69 with 44 (2775),
+// 73 with 55 (2220), 66 with 66 (1887) and 71 with 77; 1296x864 62 with 22, 54 with 33, 50
+// with 44 (1800), 54 with 55; 979x546 47, 36 and 40 with 11, 22 (1725) and 33; 2048x2048
+// 137 with 77, 125 with 99 (2961), 141 with 132.
+int64_t ssim_cost(int64_t tiles, int rows) {
+  constexpr int kOf[kSsimOccupancy] = {0, 6, 7}, kFull = 10;
+  const int64_t per_simd = (3 * tiles + kSimds - 1) / kSimds;
+  return (per_simd / kSsimOccupancy * kFull + kOf[per_simd % kSsimOccupancy]) * (rows + 4 * R);
 }
 
-// Shape of k_ssim's launch: rows of a tile, tiles, and whether a wavefront (one channel)
-// is a workgroup.  A tile of r rows passes over r + 4R, so taller is less work, but all
-// its rows one after the other: the shape is the one whose rounds of as many wavefronts
-// as fit on the chip, times the rows of a round, are fewest.  1296x864 takes 57 us with
-// 34 rows (one round), 64 with 45, 67 with 23; 10.1 Mpix 285 with 89, 331 with 34 or
-// 122; 0.2 Mpix 28 with 12, 33 with 23.  Three wavefronts (the channels) share a
-// workgroup and one sum only where single sums might not fit.
-struct SsimShape {
-  int rows, tiles, parts;
-  bool waves;
-};
-SsimShape ssim_shape(const ViewDev* hviews, int V) {
-  SsimShape best{};
-  double best_cost = 0.0;
-  for (int rows = 12; rows <= 133; rows += TAPS) {   // with 2R more, whole runs of TAPS rows
-    const int64_t t = ssim_tiles(hviews, V, rows);
-    const bool fits = 3 * t <= kSsimParts;
-    if (!fits && rows < LT) continue;   // (from LT rows on there are no more tiles than loss_tiles() counts)
-    const double rounds = (double)((3 * t + kSsimWaves - 1) / kSsimWaves), cost = (rows + 4 * R) * rounds;
-    if (best_cost == 0.0 || cost < best_cost) {
-      best = SsimShape{rows, (int)t, (int)(fits ? 3 * t : t), fits};
-      best_cost = cost;
-    }
-  }
-  return best;
+// Rows of a view's blocks, in TAPS, by the view alone (its sums have to be its own): a part
+// of the strip that is best for it alone, so that this is made of them, and small, so that
+// the strips of a batch can be; but no more blocks than k_loss_final adds up at no cost.
+int ssim_block(const ViewDev& v) {
+  const int64_t cols = ceil_div(v.W, SW);
+  int best = 1;
+  for (int r = 2; r <= kMaxRows; ++r)
+    if (ssim_cost(cols * ceil_div(v.H, TAPS * r), TAPS * r) < ssim_cost(cols * ceil_div(v.H, TAPS * best), TAPS * best))
+      best = r;
+  int b = 1;
+  while (b < best && (best % b != 0 || 3 * cols * ceil_div(v.H, TAPS * b) > 4096)) ++b;
+  return b;
 }
+static_assert(SW >= LT && 3 * TAPS >= LT && kLossSums >= (size_t)9 * kLossTiles,
+              "at most three blocks, of three channels, to a 32x32 tile");
 }  // namespace
 
-int loss_partials(const ViewDev* hviews, int V) {
-  const int t = loss_tiles(hviews, V), p = ssim_shape(hviews, V).parts;
-  return t > p ? t : p;
+LossPlan loss_plan(const ViewDev* hviews, int V, bool ssim) {
+  LossPlan p{};
+  if (!ssim) {
+    for (int v = 0; v < V; ++v)
+      p.tiles.off[v + 1] = p.tiles.off[v] + ceil_div(hviews[v].W, LT) * ceil_div(hviews[v].H, LT);
+    p.sums = p.tiles;
+    return p;
+  }
+  for (int v = 0; v < V; ++v) {
+    const int b = ssim_block(hviews[v]);
+    p.block[v] = (uint8_t)b;
+    p.sums.off[v + 1] = p.sums.off[v] + 3 * ceil_div(hviews[v].W, SW) * ceil_div(hviews[v].H, TAPS * b);
+  }
+  // blocks of a strip: as many as fit the height that is best for the batch
+  int64_t best_cost = 0;
+  for (int r = 1; r <= kMaxRows; ++r) {
+    int64_t tiles = 0;
+    int rows = 0;
+    for (int v = 0; v < V; ++v) {
+      const int h = TAPS * p.block[v] * (r > p.block[v] ? r / p.block[v] : 1);
+      tiles += (int64_t)ceil_div(hviews[v].W, SW) * ceil_div(hviews[v].H, h);
+      rows = h > rows ? h : rows;
+    }
+    const int64_t cost = ssim_cost(tiles, rows);
+    if (r > 1 && cost >= best_cost) continue;
+    best_cost = cost;
+    for (int v = 0; v < V; ++v) p.blocks[v] = (uint8_t)(r > p.block[v] ? r / p.block[v] : 1);
+  }
+  for (int v = 0; v < V; ++v)
+    p.tiles.off[v + 1] = p.tiles.off[v] + ceil_div(hviews[v].W, SW) *
+                                              ceil_div(hviews[v].H, TAPS * p.block[v] * p.blocks[v]);
+  return p;
 }
 
-hipError_t launch_loss_dev(const ViewDev* dviews, const ViewDev* hviews, int V, const float* color,
+hipError_t launch_loss_dev(const ViewDev* dviews, int V, const LossPlan& plan, const float* color,
                            const float* target, float w_l1, float w_dssim, double* partials, double* loss_out,
                            float* dL_dcolor, hipStream_t s) {
   Win win;
@@ -502,28 +576,17 @@ hipError_t launch_loss_dev(const ViewDev* dviews, const ViewDev* hviews, int V, 
   }
   for (int k = 0; k < TAPS; ++k) win.w[k] = (float)(g[k] / tot);
   const bool ssim = w_dssim != 0.0f;
-  const SsimShape sh = ssim ? ssim_shape(hviews, V) : SsimShape{};
-  const int rows = ssim ? sh.rows : LT, cols = ssim ? SW : LT;
-  LossTiles lt{};
-  int t = 0;
-  for (int v = 0; v < V; ++v) {
-    lt.off[v] = t;
-    t += ((hviews[v].W + cols - 1) / cols) * ((hviews[v].H + rows - 1) / rows);
-  }
-  lt.off[V] = t;
   double2* part = reinterpret_cast<double2*>(partials);
-  const dim3 grid(kXcds * xcd_tile_chunk(ssim ? sh.parts : t));   // at least as many workgroups, see xcd_tile
+  // at least as many workgroups as tiles, see xcd_tile
+  const dim3 grid(kXcds * xcd_tile_chunk((ssim ? 3 : 1) * plan.tiles.off[V]));
   if (!ssim)
-    hipLaunchKernelGGL(k_l1, grid, dim3(256), 0, s, dviews, V, lt, color, target, w_l1, dL_dcolor, part);
-  else if (sh.waves)
-    hipLaunchKernelGGL(k_ssim<1>, grid, dim3(64), 0, s, dviews, V, lt, rows, color, target, win, w_l1, w_dssim,
-                       dL_dcolor, part);
+    hipLaunchKernelGGL(k_l1, grid, dim3(256), 0, s, dviews, V, plan.tiles, color, target, w_l1, dL_dcolor, part);
   else
-    hipLaunchKernelGGL(k_ssim<3>, grid, dim3(192), 0, s, dviews, V, lt, rows, color, target, win, w_l1, w_dssim,
-                       dL_dcolor, part);
+    hipLaunchKernelGGL(k_ssim, grid, dim3(64), 0, s, dviews, V, plan, color, target, win, w_l1, w_dssim, dL_dcolor,
+                       partials);
   if (loss_out)
-    hipLaunchKernelGGL(k_loss_final, dim3(V), dim3(256), 0, s, dviews, lt, part, ssim && sh.waves ? 3 : 1, w_l1,
-                       w_dssim, ssim ? 1 : 0, loss_out);
+    hipLaunchKernelGGL(k_loss_final, dim3(V), dim3(kFinalThreads), 0, s, dviews, plan.sums, part, w_l1, w_dssim, ssim ? 1 : 0,
+                       loss_out);
   return hipGetLastError();
 }
 
