@@ -179,7 +179,8 @@ gs_status gs_render_fwd(gs_ctx* ctx, float* color, gs_stream stream);
  * device images (layout above).  loss_out: device, n_views doubles (per-view
  * loss), may be NULL.  dL_dcolor: device image receiving dL/dcolor of the sum of
  * the per-view losses (sign(0) = 0 for the L1 term).  A view's loss and gradient
- * are the same bits alone and in any batch. */
+ * are the same bits alone and in any batch.  dL_dcolor may overlap color or target:
+ * with w_dssim != 0 it then goes through a context buffer. */
 gs_status gs_loss(gs_ctx* ctx, const float* color, const float* target, float w_l1, float w_dssim,
                   double* loss_out, float* dL_dcolor, gs_stream stream);
 
@@ -189,10 +190,12 @@ gs_status gs_loss(gs_ctx* ctx, const float* color, const float* target, float w_
  * device array of the library (9 MiB per GPU, held until the process ends) instead
  * of context memory; it calls no allocating routine.  Limit: at most 65536 32x32
  * loss tiles summed over the context's views (ceil(W/32) ceil(H/32) per view,
- * about 67 Mpix); beyond it GS_ERR_CAPACITY and nothing is queued.  Every call on
- * one GPU shares that array, from any context or stream: calls that overlap on a
- * GPU race and must be ordered by the caller.  Nothing in it needs clearing (each
- * call writes every sum before reading it). */
+ * about 67 Mpix); beyond it GS_ERR_CAPACITY and nothing is queued.  A dL_dcolor
+ * that overlaps color or target goes through the array with w_dssim != 0, beside
+ * the sums: views of more than about 0.7 Mpix in all give GS_ERR_CAPACITY likewise.
+ * Every call on one GPU shares that array, from any context or stream: calls that
+ * overlap on a GPU race and must be ordered by the caller.  Nothing in it needs
+ * clearing (each call writes every sum before reading it). */
 gs_status gs_loss_noalloc(gs_ctx* ctx, const float* color, const float* target, float w_l1, float w_dssim,
                           double* loss_out, float* dL_dcolor, gs_stream stream);
 

@@ -24,7 +24,8 @@ struct DevBuf {
 enum Stage { kNone = 0, kProjected = 1, kBinned = 2, kRendered = 3 };
 
 // Scratch of gs_loss_noalloc: the loss sums of its largest views, 9 MiB that every GPU
-// the library runs on holds until the process ends.
+// the library runs on holds until the process ends (after the sums, a gradient on its way
+// to where an image lies).
 // In host code this name is a host-side stand-in, not a device address: host code
 // uses the per-device address gs_create looks up (scratch_ptr).
 static __device__ __align__(256) double scratch[2 * kLossSums];
@@ -173,6 +174,14 @@ struct Prof {
 };
 
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
+
+// A loss gradient written over one of the images (of `bytes` bytes) goes through a buffer:
+// the SSIM term reads both around every pixel.
+bool loss_via_buffer(const float* color, const float* target, const float* grad, size_t bytes, float w_dssim) {
+  const uintptr_t g = (uintptr_t)grad;
+  const auto over = [&](const float* im) { return g < (uintptr_t)im + bytes && (uintptr_t)im < g + bytes; };
+  return w_dssim != 0.0f && (over(color) || over(target));
+}
 
 int ceil_log2(uint64_t x) {
   int b = 0;
@@ -666,14 +675,8 @@ gs_status gs_loss(gs_ctx* c, const float* color, const float* target, float w_l1
   gs_status st;
   const LossPlan plan = loss_plan(c->hviews.data(), c->V, w_dssim != 0.0f);
   if ((st = ensure(c, c->lossp, (size_t)plan.sums.off[c->V] * 16, s)) != GS_OK) return st;
-  // a gradient written over one of the images goes through a buffer: the SSIM term
-  // reads both around every pixel
   const size_t image = (size_t)c->P * 3 * 4;
-  const auto over = [&](const float* im) {
-    const uintptr_t d = (uintptr_t)dL_dcolor, i = (uintptr_t)im;
-    return d < i + image && i < d + image;
-  };
-  const bool via = w_dssim != 0.0f && (over(color) || over(target));
+  const bool via = loss_via_buffer(color, target, dL_dcolor, image, w_dssim);
   if (via && (st = ensure(c, c->aux, image, s)) != GS_OK) return st;
   Prof pr(c, GS_K_LOSS, s);
   GS_HIP(c, launch_loss_dev(c->views.as<ViewDev>(), c->V, plan, color, target, w_l1, w_dssim, c->lossp.as<double>(),
@@ -703,8 +706,18 @@ gs_status gs_loss_noalloc(gs_ctx* c, const float* color, const float* target, fl
   GS_HIP(c, hipSetDevice(c->device));
   // every sum is written before it is read: nothing to clear
   const LossPlan plan = loss_plan(c->hviews.data(), c->V, w_dssim != 0.0f);
+  const size_t sums = (size_t)plan.sums.off[c->V] * 16, image = (size_t)c->P * 3 * 4;
+  const bool via = loss_via_buffer(color, target, dL_dcolor, image, w_dssim);
+  if (via && sums + image > sizeof scratch) {
+    char buf[160];
+    std::snprintf(buf, sizeof buf, "gs_loss_noalloc: dL_dcolor overlaps an image, and the %zu bytes it would go "
+                                   "through do not fit in the library's array", image);
+    return fail(c, GS_ERR_CAPACITY, buf);
+  }
+  float* grad = via ? reinterpret_cast<float*>(static_cast<char*>(sp) + sums) : dL_dcolor;
   GS_HIP(c, launch_loss_dev(c->views.as<ViewDev>(), c->V, plan, color, target, w_l1, w_dssim,
-                            reinterpret_cast<double*>(sp), loss_out, dL_dcolor, (hipStream_t)stream));
+                            reinterpret_cast<double*>(sp), loss_out, grad, (hipStream_t)stream));
+  if (via) GS_HIP(c, hipMemcpyAsync(dL_dcolor, grad, image, hipMemcpyDeviceToDevice, (hipStream_t)stream));
   return GS_OK;
 }
 

@@ -1,0 +1,61 @@
+"""gs_loss_noalloc with its gradient written over one of the images: the same bits as into
+a buffer of its own where the library's array holds the gradient meanwhile, refused before
+anything is queued where it does not, and of no matter to the L1 term alone."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2503_13086_amd as gs
+from paper_2503_13086_amd.pipeline import Rasterizer
+from tests.test_gpu_loss_batches import _images, _loss, _views
+
+pytestmark = pytest.mark.gpu
+
+
+def _in_place(rz, sizes, x, y, over, w_dssim):
+    """Loss values and gradient of a call whose gradient lies over x or y, shift elements on."""
+    image, shift = over
+    n = x.numel()
+    buf = torch.zeros(n + shift, device="cuda")
+    buf[:n] = x if image == "color" else y
+    x, y = (buf[:n], y) if image == "color" else (x, buf[:n])
+    lo = torch.full((len(sizes),), -1.0, dtype=torch.float64, device="cuda")
+    gs.gs_loss_noalloc(rz.ctx, x, y, 0.8, w_dssim, lo, buf[shift:])
+    torch.cuda.synchronize()
+    return lo.cpu().numpy(), buf[shift:].clone()
+
+
+@pytest.mark.parametrize("over", [("color", 0), ("target", 0), ("color", 5), ("target", 3001)])
+@pytest.mark.parametrize("sizes", [[(1, 1)], [(32, 32)], [(32, 32)] * 64, [(150, 101), (77, 45)],
+                                   [(979, 546), (500, 400)]],
+                         ids=lambda s: "%d_of_%dx%d" % (len(s), *s[0]))
+def test_same_as_out_of_place(sizes, over):
+    x, y = _images(sum(w * h for w, h in sizes), 3)
+    if over[1] >= x.numel():
+        pytest.skip("no overlap left")
+    rz = Rasterizer(0)
+    try:
+        lo, dl = _loss(rz, sizes, x, y, 0.8, 0.2, gs.gs_loss_noalloc)
+        li, di = _in_place(rz, sizes, x, y, over, 0.2)
+        assert np.array_equal(lo, li) and torch.equal(dl, di)
+    finally:
+        rz.close()
+
+
+def test_refused_where_the_array_is_too_small():
+    sizes = [(1600, 1067)]
+    x, y = _images(1600 * 1067, 4)
+    rz = Rasterizer(0)
+    try:
+        _views(rz, sizes)
+        before, lo = x.clone(), torch.full((1,), -1.0, dtype=torch.float64, device="cuda")
+        with pytest.raises(gs.GsError) as ei:
+            gs.gs_loss_noalloc(rz.ctx, x, y, 0.8, 0.2, lo, x)
+        torch.cuda.synchronize()
+        assert ei.value.status == gs.GS_ERR_CAPACITY and "overlaps" in str(ei.value)
+        assert torch.equal(x, before) and float(lo[0]) == -1.0
+        one, dl = _loss(rz, sizes, x, y, 0.8, 0.0, gs.gs_loss_noalloc)     # L1 alone: pixel by pixel
+        li, di = _in_place(rz, sizes, x, y, ("color", 0), 0.0)
+        assert np.array_equal(one, li) and torch.equal(dl, di)
+    finally:
+        rz.close()
