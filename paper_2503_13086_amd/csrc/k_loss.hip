@@ -216,8 +216,8 @@ __device__ inline double whole_sums(double x) {
 // windows' multiply-adds) and the 22 16-byte LDS accesses a row beside it.  It replaced
 // two kernels over 32x32 tiles with the statistics in HBM between them (36 bytes a pixel
 // written and read) and, for gs_loss_noalloc, one over 52x52 patches: 10.1 Mpix in 9
-// views 427 -> 299 us (both terms and the final sums), 1600x1067 88 -> 74, 1296x864
-// 63 -> 53, three views of 0.2 Mpix in all 38 -> 23.
+// views 426 -> 282 us (both terms and the final sums), 1600x1067 87 -> 74, 1296x864
+// 63 -> 54, three views of 0.2 Mpix in all 38 -> 23.
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kSsimOccupancy))) void k_ssim(
     const ViewDev* __restrict__ views, int V, LossPlan plan, const float* __restrict__ x,
     const float* __restrict__ y, Win win, float w_l1, float w_dssim, float* __restrict__ grad,
@@ -378,20 +378,26 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kSsimOccupan
   }
 }
 
-// One workgroup per view: the view's partial sums added up in FP64.
-constexpr int kFinalThreads = 256;
-__global__ __launch_bounds__(kFinalThreads) void k_loss_final(const ViewDev* __restrict__ views, LossOffsets lt,
-                                                              const double2* __restrict__ partials, float w_l1,
-                                                              float w_dssim, int ssim, double* __restrict__ out) {
-  __shared__ double sh[kFinalThreads / 64];
+// One workgroup per view: the view's partial sums added up in FP64, kFinalBatch loads of a
+// thread in flight (7110 sums of 1296x864 are two round trips to memory).
+constexpr int kFinalBatch = 16;
+__global__ __launch_bounds__(256) void k_loss_final(const ViewDev* __restrict__ views, LossOffsets lt,
+                                                     const double2* __restrict__ partials, float w_l1,
+                                                     float w_dssim, int ssim, double* __restrict__ out) {
+  __shared__ double sh[4];
   const int v = blockIdx.x;
   const ViewDev& cv = views[v];
+  const int end = lt.off[v + 1];
   double a = 0.0, b = 0.0;
-#pragma unroll 4
-  for (int t = lt.off[v] + threadIdx.x; t < lt.off[v + 1]; t += kFinalThreads) {
-    const double2 pt = partials[t];
-    a += pt.x;
-    b += pt.y;
+  for (int t = lt.off[v] + threadIdx.x; t < end; t += 256 * kFinalBatch) {
+    double2 pt[kFinalBatch];
+#pragma unroll
+    for (int k = 0; k < kFinalBatch; ++k) pt[k] = t + 256 * k < end ? partials[t + 256 * k] : make_double2(0.0, 0.0);
+#pragma unroll
+    for (int k = 0; k < kFinalBatch; ++k) {
+      a += pt[k].x;
+      b += pt[k].y;
+    }
   }
   a = block_sum_d(a, sh);
   b = block_sum_d(b, sh);
@@ -496,21 +502,19 @@ int loss_tiles(const ViewDev* hviews, int V) {
 }
 
 namespace {
-constexpr int kSimds = 1024;
+constexpr int kSsimWaves = 1024 * kSsimOccupancy;   // wavefronts the chip holds at once
 
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // A strip of r rows passes over r + 4R, so taller is less work, but all its rows one after
-// the other.  A row takes 0.6 us with one wavefront to a SIMD, 0.7 with two and 1.0 with
-// the three that fit, so what a launch takes goes with its rows times that, summed over
-// the rounds.  Measured: 1600x1067 77 us with 33 rows (3663 wavefronts), 69 with 44 (2775),
-// 73 with 55 (2220), 66 with 66 (1887) and 71 with 77; 1296x864 62 with 22, 54 with 33, 50
-// with 44 (1800), 54 with 55; 979x546 47, 36 and 40 with 11, 22 (1725) and 33; 2048x2048
-// 137 with 77, 125 with 99 (2961), 141 with 132.
+// the other: what a launch takes goes with the rounds of as many wavefronts as fit on the
+// chip times the rows of a round.  In a training step (the target out of the caches)
+// 1296x864 takes 62 us with strips of 22 rows (3600 wavefronts), 58 with 33 (2430), 63 with
+// 44; 1600x1067 81 with 33 (3663), 72 with 44 (2775), 78 with 55; 2048x2048 148 with 77
+// (3807), 126 with 99 (2961), 142 with 110; two views of 1296x864 94 with 44 (3600), 83
+// with 55 (2880), 90 with 66; ten megapixels in nine views 290 with 132 (5922), 296 with 88.
 int64_t ssim_cost(int64_t tiles, int rows) {
-  constexpr int kOf[kSsimOccupancy] = {0, 6, 7}, kFull = 10;
-  const int64_t per_simd = (3 * tiles + kSimds - 1) / kSimds;
-  return (per_simd / kSsimOccupancy * kFull + kOf[per_simd % kSsimOccupancy]) * (rows + 4 * R);
+  return (3 * tiles + kSsimWaves - 1) / kSsimWaves * (rows + 4 * R);
 }
 
 // Rows of a view's blocks, in TAPS, by the view alone (its sums have to be its own): a part
@@ -523,7 +527,7 @@ int ssim_block(const ViewDev& v) {
     if (ssim_cost(cols * ceil_div(v.H, TAPS * r), TAPS * r) < ssim_cost(cols * ceil_div(v.H, TAPS * best), TAPS * best))
       best = r;
   int b = 1;
-  while (b < best && (best % b != 0 || 3 * cols * ceil_div(v.H, TAPS * b) > 4096)) ++b;
+  while (b < best && (best % b != 0 || 3 * cols * ceil_div(v.H, TAPS * b) > 8192)) ++b;
   return b;
 }
 static_assert(SW >= LT && 3 * TAPS >= LT && kLossSums >= (size_t)9 * kLossTiles,
@@ -585,7 +589,7 @@ hipError_t launch_loss_dev(const ViewDev* dviews, int V, const LossPlan& plan, c
     hipLaunchKernelGGL(k_ssim, grid, dim3(64), 0, s, dviews, V, plan, color, target, win, w_l1, w_dssim, dL_dcolor,
                        partials);
   if (loss_out)
-    hipLaunchKernelGGL(k_loss_final, dim3(V), dim3(kFinalThreads), 0, s, dviews, plan.sums, part, w_l1, w_dssim, ssim ? 1 : 0,
+    hipLaunchKernelGGL(k_loss_final, dim3(V), dim3(256), 0, s, dviews, plan.sums, part, w_l1, w_dssim, ssim ? 1 : 0,
                        loss_out);
   return hipGetLastError();
 }
