@@ -629,7 +629,8 @@ __global__ __launch_bounds__(T * T) __attribute__((amdgpu_waves_per_eu(4))) void
     // whose cutoff ellipse meets its block, walked back to front
     uint64_t mask[NM];
     block_masks<NM>(s0, s1, min(m, wave_last - beg), qx, qy, mask);
-    const uint32_t lrel = lp > (uint32_t)beg ? lp - (uint32_t)beg : 0u;   // batch positions this pixel blended
+    // batch positions this pixel blended (at most all NB: they are compared as byte offsets)
+    const uint32_t lrel = lp > (uint32_t)beg ? min(lp - (uint32_t)beg, (uint32_t)NB) : 0u;
     int cnt = 0;
     bool opaque = false, wild_colour = false;
 #pragma unroll
