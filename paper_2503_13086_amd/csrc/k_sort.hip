@@ -229,10 +229,11 @@ __global__ __launch_bounds__(kChunkScanThreads) void k_radix_chunk_scan(uint32_t
 // workgroup itself, in place of launches of 4 to 5 us each: up to kDirectBlocks blocks
 // the histogram's own rows (a pass is then two launches), up to kDirectChunks chunks
 // the chunk sums (three).  A row is 1 KB, read from L2, 32 rows in flight.  The lines:
-// a depth sort of 73 blocks took 75.9 us scanned, 69.2 adding its 5 chunk sums, 64.9
-// adding its rows (of 3 blocks: 63.0, 57.9, 48.7); of 733 blocks, 46 chunks, 120 us
-// scanned and 115 adding chunk sums; of 2198 blocks, 69 chunks of 32, 241 us scanned
-// and 268 adding chunk sums.
+// a depth sort of 3 blocks takes 63.0 us scanned, 57.9 adding chunk sums and 48.7 adding
+// its rows; of 73 blocks 75.9, 65.8 and 62.5; with chunk sums or rows, 98 blocks take 67.3
+// and 67.1 us, 110 67.6 and 67.8, 128 67.7 and 69.3, 146 69.9 and 73.7, 256 76.3 and 91.2
+// (the line is the power of two where the two part).  Of 733 blocks, 46 chunks, 120 us
+// scanned and 115 adding chunk sums; of 2198 blocks, 69 chunks of 32, 241 and 268.
 constexpr int kDirectBlocks = 128, kDirectChunks = 64;
 enum StartsFrom { kScanned, kBlockRows, kChunkSums };
 struct DigitStarts {
@@ -532,9 +533,11 @@ __global__ __launch_bounds__(1024) void k_scan_blocks(uint32_t* __restrict__ blo
 }
 
 // Up to so many blocks the last workgroup of k_scan_reduce to finish scans their sums
-// itself (a launch less, about 4 us of each binning); beyond it k_scan_blocks does, with
-// its 1024 threads.
-constexpr int kLastBlockScan = 256;
+// itself, beyond it k_scan_blocks does: a launch less, but every workgroup counts itself
+// off on one address.  Count and scan of 73 blocks take 34.3 us and 35.3 with the launch,
+// of 98 36.8 and 37.8, of 128 38.1 and 38.1, of 171 41.0 and 40.4, of 256 46.3 and 43.9, of
+// 488 65.9 and 57.9.
+constexpr int kLastBlockScan = 128;
 
 // Sums of the counts of every 64 consecutive depth-ordered entries (group_sums,
 // one per wave of the emission) and of every kScanItems entries (block_sums).
