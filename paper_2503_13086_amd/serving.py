@@ -282,11 +282,12 @@ class Engine:
         counts and emission info, 2D gradient, histograms, split-work lists), 16 B
         per pair (tile ids and record ids, ping-pong), the buffers' 25 %
         over-allocation and 320 KiB of fixed buffers (status and split counters,
-        the split lists' floors, small scratch); 100 B per pixel (per-pixel forward
-        state, soft count and its gradient, image and dL/dimage, and 36 B to spare)."""
+        the split lists' floors, small scratch); 64 B per pixel (per-pixel forward
+        state, soft count and its gradient, 25 B with the over-allocation, image and
+        dL/dimage 24, the views' targets side by side 12, tile ranges and loss sums)."""
         pairs = self.pairs_per_view if self.pairs_per_view is not None else 16 * n
         ctx = int((142 * n + 16 * pairs) * 5 // 4) + 327680
-        return ctx + 100 * pixels
+        return ctx + 64 * pixels
 
     def _resident_bytes(self, n_total: int, extra_targets: int) -> int:
         tgt = sum(t.numel() * 4 for t in self.targets) + extra_targets
