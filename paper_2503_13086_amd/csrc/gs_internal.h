@@ -53,9 +53,8 @@ __host__ __device__ inline int n_sh(int D) { return (D + 1) * (D + 1); }
 // holds the centre, else the smallest of the minima along the four edges (clamped
 // 1-D minimisers, nbc = -b/c, nba = -b/a).  FP64, no contraction, fixed operation
 // order: every kernel that asks gets the same answer.  The pair lists are defined
-// by this test on the FP64 conic and cutoff of the projection (exact_cutoff_geo);
-// cutoff_geo below builds the same structure from a record's fp32 copies, which
-// only the fp32 clear-case test uses.
+// by this test on the FP64 conic and cutoff of the projection (exact_cutoff_geo); the
+// fp32 test below it settles the clear cases from a record's fp32 copies.
 struct CutoffGeo {
   double u, w, a, b, c, nbc, nba, lim;
 };

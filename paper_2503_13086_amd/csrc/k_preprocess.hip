@@ -375,20 +375,19 @@ __device__ inline void finish_geom(const float* P, int stride, int g, const floa
   for (int r = 0; r < 11; ++r) out[r] = (float)outv[r];
 }
 
-// With adam != 0 the gradient is applied at once (params updated in place, `out`
-// written only when not NULL); otherwise it goes to `out` (or is added to it).
-// One kernel serves both so that the gradient is the same machine arithmetic
-// either way.  The parameters are read before this thread writes any of them,
-// and a thread touches only its own Gaussian's column.
-// What a backward kernel does with the gradient it forms.  kBwdAdamBig: the parameters
-// are written past the caches (apply_rows).
+// What a backward kernel does with the gradient it forms: stores it, adds it to what is
+// there, or applies it at once (the parameters updated in place), with the gradient
+// written as well (kBwdAdamStore) or the parameters written past the caches
+// (kBwdAdamBig, see apply_rows).
 enum BwdOut { kBwdStore, kBwdAccumulate, kBwdAdam, kBwdAdamStore, kBwdAdamBig };
 
 constexpr int kRowGroup = 4;   // rows whose loads are in flight (6: 5 % slower with many views, 8 spills)
 
 // Stores the gradient of every row, adds it to what is there, or applies it at once
-// (fused step).  f holds the SH rows of P.  The kernels share this function, so the
-// gradient is the same machine arithmetic either way.
+// (fused step).  f holds the SH rows of P.  A gradient is the same bits whatever is done
+// with it: the instantiations share every function that forms it, and the row's Adam
+// arithmetic is outside contraction (tests compare them bit for bit, since which products
+// and sums of the shared functions are contracted is the compiler's choice).
 // The fused step is bound by HBM: every row of P, M and V read and written once.  Rows
 // go in groups of kRowGroup, the loads of the next group issued before this group's
 // arithmetic and stores (rows of one thread never alias: each group's loads precede its

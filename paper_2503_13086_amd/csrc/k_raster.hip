@@ -215,8 +215,8 @@ __device__ inline uint32_t shift_in(uint32_t x, uint64_t m) {
 }
 
 // Candidates a wavefront takes together in the forward: their tests and alphas do not
-// depend on each other.  1, 2 or 4 took 692, 657 and 667 us at 1M Gaussians and 10
-// Mpix (six to eight wavefronts per SIMD hide most of it) and 74, 64 and 60 us at 10k
+// depend on each other.  One build with 1, 2 or 4 took 692, 657 and 667 us at 1M
+// Gaussians and 10 Mpix (six to eight wavefronts per SIMD hide most of it) and 74, 64 and 60 us at 10k
 // Gaussians and 128x128 pixels (256 wavefronts on the whole chip).
 constexpr int kFwdGroup = 4;
 
@@ -229,9 +229,9 @@ constexpr int kFwdGroup = 4;
 // broadcast.  Bound by VALU issue: about 55 cycles per candidate and wavefront (a
 // selection of masks held in scalar registers keeps comparisons, selects and scalar
 // operands, four cycles each, to five), 85% of the issue slots taken, where one
-// workgroup per tile with a barrier per batch took 81: 722 -> 667 us at 1M
-// Gaussians, nine views and 10 Mpix, 95 -> 82 us at 300k and 1296x864, 77 -> 60 us at
-// 10k and 128x128.
+// workgroup per tile with a barrier per batch took 81: in a training step of 1M
+// Gaussians, nine views and 10 Mpix 751 -> 699 us, of 300k and 1296x864 101 -> 87, of 10k
+// and 128x128 78 -> 59.
 template <int T>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k_render_fwd(
     const ViewDev* __restrict__ views, int V, int n_tiles, const uint2* __restrict__ ranges,
@@ -499,8 +499,10 @@ __device__ inline float fold_mirror_bit2(float a, float b) {
 constexpr int kPanel = 8;
 // Candidates whose tests and alphas a wavefront takes together (each wavefront's
 // chain per candidate is long, and four wavefronts per SIMD hide it only in part):
-// 1, 2 or 4 at a time took 1.48, 1.33 and 1.26 ms at 1M Gaussians and 10 Mpix, and
-// 117, 86 and 76 us at 10k Gaussians and 128x128 pixels.
+// one build with 1, 2 or 4 at a time took 1.48, 1.33 and 1.26 ms at 1M Gaussians and 10
+// Mpix, and 117, 86 and 76 us at 10k Gaussians and 128x128 pixels.  In a training step
+// the kernel takes 1.30 ms and 75 us there, and 146 us at 300k and 1296x864, where the
+// sums across 64 lanes took 1.69 ms, 112 and 209 us.
 constexpr int kGroup = 4;
 typedef __attribute__((address_space(3))) double LdsDouble;
 
@@ -714,7 +716,10 @@ __global__ __launch_bounds__(T * T) __attribute__((amdgpu_waves_per_eu(4))) void
       }
       __builtin_amdgcn_wave_barrier();
       // nine sums of this lane's row: the moments of dL/d(exponent) over (dx, dy,
-      // dx^2, dx dy, dy^2) and itself, and the colour partials
+      // dx^2, dx dy, dy^2) and itself, and the colour partials.  (The offsets are rounded
+      // twice, from the splat to the block and on to the pixel; against 64 bits the 2D
+      // gradients are as far off as with one rounding, 5.1e-7 to 1.2e-6 of their norm at
+      // 37k Gaussians, and eight column numbers would not fit in the registers.)
       const uint32_t off = list[wave][base + ps];
       const float2 uw = *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(s0) + off);
       const float ux = uw.x - qx;
