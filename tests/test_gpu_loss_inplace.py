@@ -25,14 +25,12 @@ def _in_place(rz, sizes, x, y, over, w_dssim):
     return lo.cpu().numpy(), buf[shift:].clone()
 
 
-@pytest.mark.parametrize("over", [("color", 0), ("target", 0), ("color", 5), ("target", 3001)])
+@pytest.mark.parametrize("over", [("color", 0), ("target", 0), ("color", 2)])
 @pytest.mark.parametrize("sizes", [[(1, 1)], [(32, 32)], [(32, 32)] * 64, [(150, 101), (77, 45)],
                                    [(979, 546), (500, 400)]],
                          ids=lambda s: "%d_of_%dx%d" % (len(s), *s[0]))
 def test_same_as_out_of_place(sizes, over):
     x, y = _images(sum(w * h for w, h in sizes), 3)
-    if over[1] >= x.numel():
-        pytest.skip("no overlap left")
     rz = Rasterizer(0)
     try:
         lo, dl = _loss(rz, sizes, x, y, 0.8, 0.2, gs.gs_loss_noalloc)

@@ -47,7 +47,7 @@ def _block_any(m, x, y):
 
 
 @pytest.mark.parametrize("opaque", [False, True])
-@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3e38])
+@pytest.mark.parametrize("value", [np.inf, np.nan, 3e38])
 @pytest.mark.parametrize("tile", [8, 16, 32])
 def test_upstream_gradient_of_one_pixel(tile, value, opaque):
     sc = _scene(opaque=opaque)
@@ -67,7 +67,7 @@ def test_upstream_gradient_of_one_pixel(tile, value, opaque):
 
 
 @pytest.mark.parametrize("opaque", [False, True])
-@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("value", [np.inf, np.nan])
 @pytest.mark.parametrize("tile", [8, 16, 32])
 def test_colour_of_a_splat_that_no_pixel_takes(tile, value, opaque):
     sc = _scene(opaque=opaque)
